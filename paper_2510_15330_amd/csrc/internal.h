@@ -68,7 +68,7 @@ struct AttnArgs {
                          // (work_split.h)
     int32_t* err;        // the device's error word
     // workspace
-    int4* cuts;          // [waves]: (request, KV head, last wave, units) of the (request, head) in
+    int4* cuts;          // [waves]: (request, KV head, last wave, 0) of the (request, head) in
                          // which wave w's range ends if it began inside the range and runs past
                          // it, else request -1; written by the attention kernel for the merge
     float2* part_ml;     // [2 * waves * G]: (running max in log2 units, sum) of each wave's two

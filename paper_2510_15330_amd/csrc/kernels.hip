@@ -700,98 +700,6 @@ __device__ __forceinline__ void fp8_step(AttnState<D>& st, const PageK<D, true> 
     }
 }
 
-// ----------------------------------------------------------------- merge ---
-// Online merge of partial pieces (m_i, l_i, o_i) of one (request, head):
-//   M = max_i m_i,  l = sum_i 2^(m_i - M) l_i,  out = sum_i 2^(m_i - M) o_i / l
-// Lane (qg, n) holds head n at dims 16 t + 4 qg .. + 3.  Pieces come in
-// batches whose loads are all issued before any is used; a piece marked dead
-// gets weight 0.
-template <int D>
-struct MergeAcc {
-    static constexpr int NT = D / 16;
-    float M = -INFINITY, l = 0.f;
-    f32x4 acc[NT];
-    __device__ __forceinline__ MergeAcc() {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    template <int K>
-    __device__ __forceinline__ void fold(float2 (&ml)[K], const f32x4 (&o)[K][NT], const bool (&live)[K]) {
-        float Mb = M;
-#pragma unroll
-        for (int j = 0; j < K; ++j) {
-            if (!live[j]) ml[j] = make_float2(-INFINITY, 0.f);
-            Mb = fmaxf(Mb, ml[j].x);
-        }
-        if (Mb > M) {             // exact: otherwise the factor is 1
-            const float r = fast_exp2(M - Mb);
-            l *= r;
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t] *= r;
-            M = Mb;
-        }
-#pragma unroll
-        for (int j = 0; j < K; ++j) {
-            const bool ok = ml[j].x != -INFINITY;
-            const float wt = ok ? fast_exp2(ml[j].x - M) : 0.f;
-            l += ok ? wt * ml[j].y : 0.f;
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t] += ok ? wt * o[j][t] : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-    }
-    // the pieces of waves wf .. wl: wave wf's is its kind-1 slot (the request
-    // starts inside its range), every later wave's its kind-0 slot; waves
-    // with no units left none.  Two pieces per round trip, in wave order;
-    // the first batch may already be in `ml0`, `o0` (loaded with the record).
-    static __device__ __forceinline__ int64_t slot_of(const AttnArgs& a, int v, int wf, int nh) {
-        return (int64_t)(2 * v + (v == wf ? 1 : 0)) * a.G + nh;
-    }
-    static __device__ __forceinline__ void load2(const AttnArgs& a, int v0, int wf, int wl, int nh, int qg,
-                                                 float2 (&ml)[2], f32x4 (&o)[2][NT]) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int v = min(v0 + j, wl);          // past wl: a re-read of wl's piece, dead below
-            const int64_t slot = slot_of(a, v, wf, nh);
-            ml[j] = a.part_ml[slot];
-#pragma unroll
-            for (int t = 0; t < NT; ++t) o[j][t] = *(const f32x4*)(a.part_o + slot * D + 16 * t + 4 * qg);
-        }
-    }
-    __device__ __forceinline__ void fold_waves(const AttnArgs& a, int wf, int wl, int P, int skew, int nh, int qg,
-                                               float2 (&ml0)[2], f32x4 (&o0)[2][NT]) {
-        const int W = a.waves;
-        // every wave holds units when the lightest weight's share of P is
-        // above one unit: (256 - k) P > C(W), C(W) <= (256 + k) W
-        const bool all_units = (int64_t)(256 - skew) * P > (int64_t)(256 + skew) * W;
-        auto has_units = [&](int v) {
-            return v <= wl && (all_units || share_bound(v, P, W, skew) < share_bound(v + 1, P, W, skew));
-        };
-        {
-            const bool live[2] = {has_units(wf), has_units(wf + 1)};
-            fold<2>(ml0, o0, live);
-        }
-        for (int v0 = wf + 2; v0 <= wl; v0 += 2) {
-            float2 ml[2];
-            f32x4 o[2][NT];
-            load2(a, v0, wf, wl, nh, qg, ml, o);
-            const bool live[2] = {has_units(v0), has_units(v0 + 1)};
-            fold<2>(ml, o, live);
-        }
-    }
-    // out[b, g G + n, dims of this lane] = acc / l, rounded to bf16
-    __device__ __forceinline__ void store(const AttnArgs& a, int b, int h, int qg) const {
-        const float inv = 1.f / l;
-        uint16_t* orow = a.out + (int64_t)b * a.o_sb + (int64_t)h * a.o_sh;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            u32x2 pk;
-            pk.x = (uint32_t)f32_to_bf16_rne(acc[t][0] * inv) | ((uint32_t)f32_to_bf16_rne(acc[t][1] * inv) << 16);
-            pk.y = (uint32_t)f32_to_bf16_rne(acc[t][2] * inv) | ((uint32_t)f32_to_bf16_rne(acc[t][3] * inv) << 16);
-            *(u32x2*)(orow + 16 * t + 4 * qg) = pk;
-        }
-    }
-};
-
 // Mark loaded registers as read.  A step reads some of its loads only on some
 // paths (the query only at a segment change, the second page only when the
 // step has one); a register whose load was never waited for on the path taken
@@ -1033,13 +941,16 @@ attn_mfma_kernel(AttnArgs a) {
         P += __builtin_amdgcn_readfirstlane(wave_sum(load_lens(b0)));
         zero_empty(b0);
     }
-    const int skew = share_skew(a.skew, P, a.waves, PP);
-    const int r0 = share_bound(w, P, a.waves, skew);
-    const int r1 = share_bound(w + 1, P, a.waves, skew);
+    const int W = min(a.waves, P);     // no more waves than units take a share
+    const int skew = share_skew(a.skew, P, W, PP);
     // wave 0 raises the length flag
     if (w == 0 && __any(bad_len) && lane == 0) atomicOr(a.err, kErrLength);
+    const int r0 = w < W ? share_bound(w, P, W, skew) : 0;
+    const int r1 = w < W ? share_bound(w + 1, P, W, skew) : 0;
     if (r0 >= r1) {
         if (lane == 0) a.cuts[w] = make_int4(-1, 0, 0, 0);
+        // a share that an extreme weight leaves empty: its piece is dead
+        if (w < W && lane < a.G) a.part_ml[2 * (int64_t)w * a.G + lane] = make_float2(-INFINITY, 0.f);
         trace_end();
         return;
     }
@@ -1347,48 +1258,213 @@ attn_mfma_kernel(AttnArgs a) {
     const int en = (e.np + PP - 1) / PP;
     if (lane == 0) {
         const bool cut = ex0 >= r0 && ex0 + en > r1;
-        const int wl = cut ? wave_of(ex0 + en - 1, P, a.waves, skew) : 0;
-        a.cuts[w] = cut ? make_int4(e.b, e.g, wl, P) : make_int4(-1, 0, 0, 0);
+        const int wl = cut ? wave_of(ex0 + en - 1, P, W, skew) : 0;
+        a.cuts[w] = cut ? make_int4(e.b, e.g, wl, 0) : make_int4(-1, 0, 0, 0);
     }
     trace_end();
 }
 
-// One wave per attention wave w: if w's range ended inside a (request, head)
-// that began in it, combine that request's pieces.
-template <int D>
-__global__ void __launch_bounds__(256) merge_kernel(AttnArgs a) {
-    if (a.k_new != nullptr) {
-        // decode step: advance the length of every request whose new row
-        // fitted (as kv_append_kernel does); flag the others
-        const int maxL = a.max_pages * kPage;
-        for (int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x; b < a.B; b += (int64_t)gridDim.x * 256) {
-            const int L = a.lens_rw[b];
-            bool ok = L >= 0 && L < maxL;
-            if (ok) {
-                const int pg = a.block_table[b * a.bt_stride + (L >> 4)];
-                ok = (unsigned)pg < (unsigned)a.num_pages;
-            }
-            if (ok) a.lens_rw[b] = L + 1;
-            else atomicOr(a.err, kErrAppendSlot);
+// ----------------------------------------------------------------- merge ---
+// Combines the pieces (m_i, l_i, o_i) of one cut (request, KV head):
+//   M = max_i m_i,  l = sum_i 2^(m_i - M) l_i,  out = sum_i 2^(m_i - M) o_i / l
+// Attention wave w's record names the (request, head) its range ends in, if
+// that began inside the range.  Its pieces are wave w's kind-1 slot and the
+// kind-0 slots of the waves up to the record's last one, each of which left
+// a piece.
+//
+// A piece is G D contiguous floats, dealt to the lanes as float4s (NK of
+// them a lane), so one piece costs NK loads and one weight per head.  The
+// pass is latency-bound: what it costs is its round trips to memory, so
+// pieces come in batches whose loads are all out before any is used, and
+// where a cut has many pieces its batches are dealt over several waves.
+template <int NK>
+struct MergeAcc {
+    float M[NK], l[NK];
+    f32x4 acc[NK];
+    __device__ __forceinline__ MergeAcc() {
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            M[k] = -INFINITY;
+            l[k] = 0.f;
+            acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
     }
-    const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * (256 / kWaveSize) + (threadIdx.x >> 6));
-    if (w >= a.waves) return;
-    const int lane = threadIdx.x & (kWaveSize - 1);
-    const int qg = lane >> 4, n = lane & 15, nh = min(n, a.G - 1);
-    // the record and, in the same round trip, the first two pieces a cut
-    // starting in wave w would have (slots 2w + 1 and 2w + 2; past the
-    // workspace's last wave a re-read of 2w + 1)
+    // a dead piece (past the last one, or of an empty share) has m = -inf:
+    // weight 0, its values unused
+    template <int K>
+    __device__ __forceinline__ void fold(const float2 (&ml)[K][NK], const f32x4 (&o)[K][NK]) {
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            float Mb = M[k];
+#pragma unroll
+            for (int j = 0; j < K; ++j) Mb = fmaxf(Mb, ml[j][k].x);
+            if (Mb > M[k]) {          // exact: otherwise the factor is 1
+                const float r = fast_exp2(M[k] - Mb);
+                l[k] *= r;
+                acc[k] *= r;
+                M[k] = Mb;
+            }
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                const bool ok = ml[j][k].x != -INFINITY;
+                const float wt = ok ? fast_exp2(ml[j][k].x - M[k]) : 0.f;
+                l[k] += ok ? wt * ml[j][k].y : 0.f;
+                acc[k] += ok ? wt * o[j][k] : f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+    }
+};
+
+// What both merge kernels share: this lane's float4s of a piece and the
+// loads and stores they make.
+template <int D, int NK>
+struct MergeLane {
+    static constexpr int DL = D / 4;             // float4s of one head's row
+    const AttnArgs& a;
+    int lane, units;                             // units: float4s of a piece
+    int hk[NK], uk[NK];                          // this lane's float4s and their heads (past the end: the last)
+    int first;                                   // the wave's first float4
+    __device__ __forceinline__ MergeLane(const AttnArgs& args, int f0 = 0) : a(args), first(f0) {
+        lane = threadIdx.x & (kWaveSize - 1);
+        units = a.G * DL;
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            uk[k] = min(first + lane + kWaveSize * k, units - 1);
+            hk[k] = uk[k] / DL;
+        }
+    }
+    __device__ __forceinline__ void load(int64_t piece, float2 (&ml)[NK], f32x4 (&o)[NK]) const {
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            ml[k] = a.part_ml[piece * a.G + hk[k]];
+            o[k] = *(const f32x4*)(a.part_o + (piece * units + uk[k]) * 4);
+        }
+    }
+    // fold the pieces of waves v0 .. min(v0 + K - 1, wl), all loaded before
+    // any is used; wave wf's is its kind-1 slot, the others' their kind-0 slot
+    template <int K>
+    __device__ __forceinline__ void fold(MergeAcc<NK>& m, int v0, int wf, int wl) const {
+        float2 ml[K][NK];
+        f32x4 o[K][NK];
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const int v = min(v0 + j, wl);       // past wl: wl's piece again, dead
+            load(2 * (int64_t)v + (v == wf ? 1 : 0), ml[j], o[j]);
+            if (v0 + j > wl) {
+#pragma unroll
+                for (int k = 0; k < NK; ++k) ml[j][k].x = -INFINITY;
+            }
+        }
+        m.template fold<K>(ml, o);
+    }
+    // out[b, g G + h, dims of this lane] = acc / l, rounded to bf16
+    __device__ __forceinline__ void store(const MergeAcc<NK>& m, int b, int g) const {
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            if (first + lane + kWaveSize * k >= units) continue;
+            const float inv = 1.f / m.l[k];
+            uint16_t* orow = a.out + (int64_t)b * a.o_sb + (int64_t)(g * a.G + hk[k]) * a.o_sh;
+            u32x2 pk;
+            pk.x = (uint32_t)f32_to_bf16_rne(m.acc[k][0] * inv) | ((uint32_t)f32_to_bf16_rne(m.acc[k][1] * inv) << 16);
+            pk.y = (uint32_t)f32_to_bf16_rne(m.acc[k][2] * inv) | ((uint32_t)f32_to_bf16_rne(m.acc[k][3] * inv) << 16);
+            *(u32x2*)(orow + 4 * (uk[k] - hk[k] * DL)) = pk;
+        }
+    }
+};
+
+// Decode step: advance the length of every request whose new row fitted (as
+// kv_append_kernel does); flag the others.
+__device__ __forceinline__ void advance_lengths(const AttnArgs& a) {
+    const int maxL = a.max_pages * kPage;
+    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < a.B; b += (int64_t)gridDim.x * blockDim.x) {
+        const int L = a.lens_rw[b];
+        bool ok = L >= 0 && L < maxL;
+        if (ok) {
+            const int pg = a.block_table[b * a.bt_stride + (L >> 4)];
+            ok = (unsigned)pg < (unsigned)a.num_pages;
+        }
+        if (ok) a.lens_rw[b] = L + 1;
+        else atomicOr(a.err, kErrAppendSlot);
+    }
+}
+
+// Pieces a batch: their loads are all in flight together, in registers.
+template <int NK>
+constexpr int kMergeBatch = NK <= 2 ? 8 : 4;
+
+// Many cuts of few pieces: one wave per attention wave.  It reads its record
+// and, in the same trip, the two pieces a cut between two long shares has.
+template <int D, int NK>
+__global__ void __launch_bounds__(kWaveSize) merge_kernel(AttnArgs a) {
+    if (a.k_new != nullptr) advance_lengths(a);
+    const int w = blockIdx.x;
+    const MergeLane<D, NK> t(a);
     const int4 c = a.cuts[w];
-    float2 ml0[2];
-    f32x4 o0[2][D / 16];
-    MergeAcc<D>::load2(a, w, w, min(w + 1, a.waves - 1), nh, qg, ml0, o0);
+    float2 ml[2][NK];
+    f32x4 o[2][NK];
+    // slots 2w + 1 and 2w + 2 (past the last wave its own again: a record
+    // there names no cut)
+    t.load(2 * (int64_t)w + 1, ml[0], o[0]);
+    t.load(2 * (int64_t)min(w + 1, a.waves - 1), ml[1], o[1]);
     if (c.x < 0) return;
-    const int b = __builtin_amdgcn_readfirstlane(c.x), g = __builtin_amdgcn_readfirstlane(c.y);
-    const int wl = __builtin_amdgcn_readfirstlane(c.z), P = __builtin_amdgcn_readfirstlane(c.w);
-    MergeAcc<D> m;
-    m.fold_waves(a, w, wl, P, share_skew(a.skew, P, a.waves, a.pp), nh, qg, ml0, o0);
-    if (n < a.G) m.store(a, b, g * a.G + n, qg);
+    MergeAcc<NK> m;
+    m.template fold<2>(ml, o);
+    const int wl = __builtin_amdgcn_readfirstlane(c.z);
+    for (int v0 = w + 2; v0 <= wl; v0 += kMergeBatch<NK>) t.template fold<kMergeBatch<NK>>(m, v0, w, wl);
+    t.store(m, __builtin_amdgcn_readfirstlane(c.x), __builtin_amdgcn_readfirstlane(c.y));
+}
+
+// Few cuts of many pieces: workgroup i takes the records of attention waves
+// R i .. R i + R - 1 (R <= 64).  A wave takes one slice of 64 float4s of
+// every piece, and the slice's pieces are dealt over the NP waves that share
+// it (NS slices, NS NP <= 16), which combine through LDS.
+constexpr int kLongWaves = 16;
+template <int D>
+__global__ void __launch_bounds__(kLongWaves * kWaveSize) merge_long_kernel(AttnArgs a, int R) {
+    constexpr int K = kMergeBatch<1>;
+    __shared__ f32x4 acc_s[kLongWaves][kWaveSize];
+    __shared__ float2 ml_s[kLongWaves][kWaveSize];
+    if (a.k_new != nullptr) advance_lengths(a);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int NS = (a.G * (D / 4) + kWaveSize - 1) / kWaveSize, NP = kLongWaves / NS;
+    const int slice = wave % NS, part = wave / NS;       // part >= NP: no pieces
+    const MergeLane<D, 1> t(a, slice * kWaveSize);
+    const int lane = t.lane;
+    const int w0 = blockIdx.x * R;
+    const bool mine = lane < R && w0 + lane < a.waves;
+    const int4 c = mine ? a.cuts[w0 + lane] : make_int4(-1, 0, 0, 0);
+    for (uint64_t left = __ballot(c.x >= 0); left != 0; left &= left - 1) {   // the same for all waves
+        const int r = __ffsll((unsigned long long)left) - 1;
+        const int wf = w0 + r, wl = __builtin_amdgcn_readlane(c.z, r);
+        const int np = min(NP, (wl - wf) / K + 1);       // waves of a slice that have pieces
+        MergeAcc<1> m;
+        if (part < np)
+            for (int v0 = wf + part * K; v0 <= wl; v0 += NP * K) t.template fold<K>(m, v0, wf, wl);
+        if (np > 1) {
+            if (part > 0 && part < np) {
+                // (a NaN sum marks a poisoned piece; alone it left M at -inf)
+                acc_s[wave][lane] = m.acc[0];
+                ml_s[wave][lane] = make_float2(m.l[0] != m.l[0] ? NAN : m.M[0], m.l[0]);
+            }
+            __syncthreads();
+            if (part == 0) {
+                for (int j0 = 1; j0 < np; j0 += 4) {
+                    float2 ml[4][1];
+                    f32x4 o[4][1];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int q = slice + NS * min(j0 + j, np - 1);
+                        ml[j][0] = ml_s[q][lane];
+                        if (j0 + j >= np) ml[j][0].x = -INFINITY;
+                        o[j][0] = acc_s[q][lane];
+                    }
+                    m.template fold<4>(ml, o);
+                }
+            }
+            __syncthreads();                             // the next cut's waves write the same arrays
+        }
+        if (part == 0) t.store(m, __builtin_amdgcn_readlane(c.x, r), __builtin_amdgcn_readlane(c.y, r));
+    }
 }
 
 }  // namespace
@@ -1486,12 +1562,36 @@ int attention_blocks_per_cu(int pages_per_step, int depth, bool fp8, int D) {
     return dispatch(D, fp8, pages_per_step, depth, true, nullptr, 0, nullptr);
 }
 
+// The merge that deals each cut's pieces over a workgroup is taken where the
+// (request, head)s are few enough that each is cut over kLongMergePieces
+// waves' ranges on average.  Kernel times, one wave a cut / a workgroup a
+// cut: one request of 2,000 tokens (8 (request, head)s over 1000 waves) 70
+// against 6.6 us (two pieces a trip before), three of up to 200 tokens 111
+// against 3.9 us; 48 requests of 6-13.5k (96 over 1024 waves: 11 pieces a
+// cut) 5.1 against 5.0 us; 32 requests over fp8 pools (256 over 2048 waves: 8
+// pieces) 6.6 against 8.8 us, where the larger workgroups' launch shows.
+constexpr int kLongMergePieces = 16;
 void launch_merge(const AttnArgs& a, hipStream_t s) {
-    const dim3 g((a.waves + 3) / 4), blk(256);
-    if (a.D == 128)
-        hipLaunchKernelGGL(merge_kernel<128>, g, blk, 0, s, a);
-    else
-        hipLaunchKernelGGL(merge_kernel<64>, g, blk, 0, s, a);
+    const bool d128 = a.D == 128;
+    if ((int64_t)a.B * a.H_kv * kLongMergePieces <= a.waves) {
+        const int R = (a.waves + 255) / 256;     // <= 64 records: at most kMaxWaves waves
+        const dim3 g((a.waves + R - 1) / R), blk(kLongWaves * kWaveSize);
+        if (d128) hipLaunchKernelGGL((merge_long_kernel<128>), g, blk, 0, s, a, R);
+        else hipLaunchKernelGGL((merge_long_kernel<64>), g, blk, 0, s, a, R);
+        return;
+    }
+    const dim3 g(a.waves), blk(kWaveSize);
+    const int units = a.G * a.D / 4;             // float4s of a piece: 16 .. 512
+    if (d128) {
+        if (units <= 64) hipLaunchKernelGGL((merge_kernel<128, 1>), g, blk, 0, s, a);
+        else if (units <= 128) hipLaunchKernelGGL((merge_kernel<128, 2>), g, blk, 0, s, a);
+        else if (units <= 256) hipLaunchKernelGGL((merge_kernel<128, 4>), g, blk, 0, s, a);
+        else hipLaunchKernelGGL((merge_kernel<128, 8>), g, blk, 0, s, a);
+    } else {
+        if (units <= 64) hipLaunchKernelGGL((merge_kernel<64, 1>), g, blk, 0, s, a);
+        else if (units <= 128) hipLaunchKernelGGL((merge_kernel<64, 2>), g, blk, 0, s, a);
+        else hipLaunchKernelGGL((merge_kernel<64, 4>), g, blk, 0, s, a);
+    }
 }
 
 }  // namespace bellman

@@ -322,6 +322,42 @@ def test_long_shares_with_weighted_split(kv, pps, depth):
         G.assert_close(got, ref, kv, f"long shares waves={waves}")
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,D,lens,kv", [
+    (1, 16, 1, 128, [3000], "bf16"),             # pieces of 8 slices, two waves a slice, several batches
+    (2, 7, 1, 128, [2500, 9], "bf16"),           # pieces of 3.5 slices
+    (3, 2, 1, 64, [300, 1, 700], "bf16"),        # a piece of half a slice; fewer units than waves
+    (1, 8, 1, 128, [20000], "fp8"),
+])
+def test_requests_cut_over_many_waves(B, Hq, Hkv, D, lens, kv):
+    # few (request, head)s, each cut over 8 waves' ranges or more: the merge
+    # that deals a cut's pieces over the waves of a workgroup
+    rng = np.random.default_rng(sum(lens))
+    case = dn.random_case(rng, B, Hq, Hkv, D, lens, kv)
+    scale = float(np.float32(1.0 / np.sqrt(D)))
+    ref = oracle_case(case, scale, kv)
+    for waves in (0, 700, 130, 17):
+        got = run_case(dev_case(case, kv), scale, max_waves=waves)
+        G.assert_close(got, ref, kv, f"many waves {B},{Hq},{Hkv},{D},{lens},{kv} waves={waves}")
+    d = dev_case(case, kv)
+    d["bt"][0, 3] = case["num_pages"] + 7        # one poisoned piece among the others
+    bl.device_errors()
+    got = run_case(d, scale)
+    assert bl.device_errors() & 4
+    assert np.all(np.isnan(got[0]))
+    if B > 1:
+        G.assert_close(got[1:], ref[1:], kv, "other requests")
+
+
+def test_shares_left_empty_by_extreme_weights():
+    # weight 511 : 1 over shares of 400 pages: some odd workgroups' waves get
+    # no unit, and the merge skips their pieces
+    rng = np.random.default_rng(77)
+    case = dn.random_case(rng, 2, 32, 8, 128, [8192, 3008], "bf16")
+    scale = float(np.float32(1.0 / np.sqrt(128)))
+    got = run_case(dev_case(case), scale, max_waves=14, xcd_skew=255, pages_per_step=2)
+    G.assert_close(got, oracle_case(case, scale), "bf16", "weights 511 : 1")
+
+
 @pytest.mark.parametrize("B,kv", [(2500, "bf16"), (8192, "fp8")])
 def test_large_batches_of_short_requests(B, kv):
     # more than 1024 requests: every attention wave reads the lengths in
