@@ -60,6 +60,17 @@ int current_device(int* dev) {
     return BELLMAN_OK;
 }
 
+// The device's compute units, in g_cu_count[dev].
+int cu_count(int dev) {
+    if (g_cu_count[dev] == 0) {
+        int cu = 0;
+        hipError_t e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess || cu < 1) return fail(BELLMAN_ERR_HIP, "multiprocessor count: %s", hipGetErrorString(e));
+        g_cu_count[dev] = cu;
+    }
+    return BELLMAN_OK;
+}
+
 // Grow the current device's workspace to at least `bytes` (no region of it
 // needs initialising).
 int ensure_workspace(int dev, size_t bytes, hipStream_t stream, char** base) {
@@ -292,12 +303,7 @@ int decode_attention(const bellman_tensor_t* q, const bellman_tensor_t* k_pages,
 
     int dev;
     if ((rc = current_device(&dev))) return rc;
-    if (g_cu_count[dev] == 0) {
-        int cu = 0;
-        hipError_t e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess || cu < 1) return fail(BELLMAN_ERR_HIP, "multiprocessor count: %s", hipGetErrorString(e));
-        g_cu_count[dev] = cu;
-    }
+    if ((rc = cu_count(dev))) return rc;
     if (pps == 0) {
         // bf16: two pages per step, or one when the block table leaves room
         // for few pages per wave (short shares: the finer step shortens the
@@ -685,25 +691,44 @@ int bellman_prefill_attention_opts(const bellman_tensor_t* q, const bellman_tens
     const size_t page_head_bytes = (size_t)ps.D * 16 * 2;
     if (!ps.fp8 && (double)B * (double)max_pages >= 2147483647.0)
         return fail(BELLMAN_ERR_UNSUPPORTED, "batch x block-table width must stay below 2^31 pages");
-    const size_t copy_bytes = ps.fp8 ? 0 : (size_t)B * (size_t)max_pages * (size_t)ps.H_kv * page_head_bytes;
     if (!ps.fp8 && (double)B * (double)max_pages * ps.H_kv * (double)page_head_bytes > 1099511627776.0)
         return fail(BELLMAN_ERR_UNSUPPORTED, "the fp16 value copy of B x maxP pages would exceed 1 TiB");
-    const size_t off_tiles = kWsHeader;
-    const size_t off_pages = off_tiles + align256((size_t)(B + 1) * 4);
-    const size_t off_req = off_pages + align256((size_t)(B + 1) * 4);
-    const size_t off_tmax = off_req + align256(ps.fp8 ? 0 : (size_t)B * (size_t)max_pages * 4);
-    const size_t off_vmax = off_tmax + align256(ps.fp8 ? 0 : (size_t)B * (size_t)max_pages * ps.H_kv * 4);
-    const size_t off_copy = off_vmax + align256((size_t)B * ps.H_kv * 4);
-    const size_t total = off_copy + align256(copy_bytes);
-
     int dev;
     if ((rc = current_device(&dev))) return rc;
+    if ((rc = cu_count(dev))) return rc;
+    // Tiles of 128 query rows (a token's G heads of a KV head each a row) x
+    // KV heads, and the attention workgroups resident at once (two a CU).
+    // Where there may be too few tiles to keep those busy, a tile's keys are
+    // cut as well, in units that still run in as many rounds as the tiles
+    // would (half a round, one a CU, where they are under a quarter of one).
+    // From two rounds on the hardware's own balance is left to do it (2048
+    // tiles, four rounds: the same uncut).  Letting 336 tiles take 1016 units
+    // instead of 488 ran the attention in 127 against 129 us and its merge in
+    // 17 against 11 us.
+    PrefillArgs a;
+    const int64_t rows = T * (H_q / ps.H_kv);
+    a.max_tiles = (rows / kPrefillRows + B) * ps.H_kv;
+    a.slots = 2 * g_cu_count[dev];
+    a.split = B <= 64 && a.max_tiles <= 2 * a.slots;
+    a.max_units = a.split ? (a.max_tiles + a.slots - 1) / a.slots * a.slots : a.max_tiles;
+
+    const bool planned = B > 64;           // by a kernel of its own (each wave plans for itself up to 64)
+    const size_t max_steps = (size_t)B * (size_t)((max_pages + 3) / 4);
+    const size_t piece_rows = a.split ? (size_t)a.max_units * kPrefillRows : 0;
+    const size_t off_tiles = kWsHeader;
+    const size_t off_ml = off_tiles + align256(planned ? (size_t)(B + 1) * 4 : 0);
+    const size_t off_o = off_ml + align256(piece_rows * sizeof(float2));
+    const size_t off_steps = off_o + align256(piece_rows * ps.D * sizeof(float));
+    const size_t off_req = off_steps + align256(planned && !ps.fp8 ? (size_t)(B + 1) * 4 : 0);
+    const size_t off_exp = off_req + align256(planned && !ps.fp8 ? max_steps * 4 : 0);
+    const size_t off_copy = off_exp + align256(ps.fp8 ? 0 : max_steps * ps.H_kv * 4);
+    const size_t total = off_copy + align256(ps.fp8 ? 0 : max_steps * ps.H_kv * 4 * page_head_bytes);
+
     hipStream_t s = (hipStream_t)stream;
     char* base;
     if ((rc = ensure_workspace(dev, total, s, &base))) return rc;
     int32_t* err;
     if ((rc = device_error_word(dev, &err))) return rc;
-    PrefillArgs a;
     a.q = (const uint16_t*)q->data;
     a.q_st = q->stride[0];
     a.q_sh = q->stride[1];
@@ -733,14 +758,15 @@ int bellman_prefill_attention_opts(const bellman_tensor_t* q, const bellman_tens
     a.fp8 = ps.fp8 ? 1 : 0;
     a.k_scale = k_pages->dequant_scale;
     a.v_scale = v_pages->dequant_scale;
-    a.page_off = (int32_t*)(base + off_pages);
-    a.page_req = (int32_t*)(base + off_req);
-    a.tmax = (float*)(base + off_tmax);
-    a.vmax = (uint32_t*)(base + off_vmax);
+    a.part_ml = (float2*)(base + off_ml);
+    a.part_o = (float*)(base + off_o);
+    a.step_off = (int32_t*)(base + off_steps);
+    a.step_req = (int32_t*)(base + off_req);
+    a.vexp = (int32_t*)(base + off_exp);
     a.vcopy = (uint16_t*)(base + off_copy);
-    // enough waves for every (page, head) tile of B x maxP pages at most
-    // once, and at most 2048 workgroups
-    a.vgrid = (int)std::max<int64_t>(1, std::min<int64_t>(2048, ((int64_t)B * max_pages * ps.H_kv + 3) / 4));
+    // a workgroup for every (step, head) tile of B x maxP pages at most once,
+    // and at most 4096
+    a.vgrid = (int)std::max<int64_t>(1, std::min<int64_t>(4096, (int64_t)max_steps * ps.H_kv));
     launch_prefill_prep(a, s);
     if ((rc = launch_status("prefill_attention (planning)"))) return rc;
     if (opts && opts->event_begin) {

@@ -104,6 +104,7 @@ struct WriteArgs {
 
 // Prompt (prefill) attention over the paged cache (prefill.hip).
 constexpr int kPrefillRows = 128;   // query rows per workgroup (4 waves x 32)
+constexpr int kPrefillKeys = 64;    // keys per step (four pages)
 struct PrefillArgs {
     const uint16_t* q;   // bf16 [T, H_q, D]
     int64_t q_st, q_sh;
@@ -119,17 +120,23 @@ struct PrefillArgs {
     float scale_log2;
     int B, T, H_q, H_kv, G, D, max_pages;
     int32_t* err;
-    int32_t* tile_start;   // workspace [B + 1]: first query tile of each request
     int fp8;               // pools of e4m3fn codes with the dequantisation scales below
     const float* k_scale;  // fp8 only, fp32 [B, H_kv]
     const float* v_scale;
-    // bf16 pools: the fp16 copy of the values the attention reads (workspace)
-    int32_t* page_off;     // [B + 1]: first copied page of each request
-    int32_t* page_req;     // [B * maxP]: the request of each copied page
-    float* tmax;           // [copied pages, H_kv]: the largest |v| of each (page, head) tile
-    uint32_t* vmax;        // [B, H_kv]: float bits of the largest |v| of each (request, KV head)
-    uint16_t* vcopy;       // [sum of copied pages, H_kv, D, 16] fp16
-    int vgrid;             // workgroups of the copy passes (4 waves each)
+    int64_t max_tiles;     // no more (tile, KV head)s, and no more units, than these
+    int64_t max_units;
+    int split;             // 1: tiles' keys may be cut into units of their own (B <= 64)
+    int slots;             // attention workgroups the device holds at once
+    // workspace
+    int32_t* tile_start;   // [B + 1]: first query tile of each request (B > 64)
+    float2* part_ml;       // [max_units, 128]: (running max in log2 units, sum) of each row of a piece
+    float* part_o;         // [max_units, 128 D]: its normalised output, in lane order
+    // bf16 pools: the fp16 copy of the values the attention reads
+    int32_t* step_off;     // [B + 1]: first copied 64-key step of each request (B > 64)
+    int32_t* step_req;     // [B * ceil(maxP / 4)]: the request of each copied step (B > 64)
+    int32_t* vexp;         // [copied steps, H_kv]: the exponent of the step's scale
+    uint16_t* vcopy;       // [copied steps, H_kv, 4 pages, D, 16] fp16
+    int vgrid;             // workgroups of the copy
 };
 
 // Launchers (kernels.hip).  They only enqueue; errors come back through
@@ -145,8 +152,8 @@ int attention_blocks_per_cu(int pages_per_step, int depth, bool fp8, int D);
 void launch_merge(const AttnArgs& a, hipStream_t s);
 // Prefill launchers (prefill.hip).
 void launch_kv_write(const WriteArgs& a, int32_t* page_start, hipStream_t s);
-// The prompt attention's planning (and, over bf16 pools, the fp16 value
-// copy), then the attention kernel itself.
+// The prompt attention's planning (B > 64) and, over bf16 pools, the fp16
+// value copy; then the attention kernel itself and the key-split merge.
 void launch_prefill_prep(const PrefillArgs& a, hipStream_t s);
 void launch_prefill_attn(const PrefillArgs& a, hipStream_t s);
 

@@ -21,6 +21,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -194,28 +195,102 @@ __global__ void lens_kernel(WriteArgs a) {
 }
 
 // --------------------------------------------------------------- planning --
-// Exclusive scan of the requests' query-tile counts, ceil(n_b / 128), into
-// tile_start[0..B].  A request whose range is malformed (longer than its
-// length, or a length past the table) gets no tiles and a flag; a q_start
-// that is not non-decreasing from a non-negative start up to at most T gives
-// no request any tile (so the tiles always fit the grid of
-// ceil(T / 128) + B workgroups).
-__device__ __forceinline__ int tiles_of(const PrefillArgs& a, int b) {
-    const int n = a.q_start[b + 1] - a.q_start[b], L = a.seq_lens[b];
-    if (n < 0 || n > L || (int64_t)L > (int64_t)a.max_pages * kPage) return -1;
-    return (n + kPrefillRows - 1) / kPrefillRows;
+constexpr int kMinChunk = 8;   // steps a unit of a key-split tile takes at least
+// A request's query rows are its n_b tokens x the G query heads of a KV
+// head, token-major (row r: token r / G, head r % G): tiles of 128 rows,
+// whose heads share the KV head's keys.  A request whose range is malformed
+// (longer than its length, or a length past the table) gets no tiles and a
+// flag; a q_start that is not non-decreasing from a non-negative start up to
+// at most T gives no request any tile (so the tiles always fit the grid).
+//
+// Where the tiles x KV heads are too few to fill the CUs, the keys of a
+// tile are cut too: request b's tiles take S_b units each, unit k the steps
+// [nt k / S_b, nt (k + 1) / S_b) of the tile's nt, and a second pass merges
+// them.  Units per KV head are numbered request by request, within one by
+// (key chunk, tile), so that neighbours read the same keys.
+//
+// Up to 64 requests every wave plans for itself from the lengths, a request
+// a lane (a planning launch took 5-6 us, and what a workgroup read back from
+// it as many round trips); beyond, prefill_plan_kernel does (no key split).
+//
+// Measured, whole prompt steps, against rows of one query head each, no key
+// split and the planning launch: one 2048-token chunk after 4,900 tokens on
+// 4/2 heads (64 tiles: 256 units of 27 steps) 171 -> 70 us, the attention
+// alone 141 -> 49 us and 7 us of merge; eight chats' 16-256 new tokens after
+// 2-8k (336 tiles instead of 416, 488 units) 207 -> 172 us; four prompts of
+// 6-12k (7584 tiles, never cut) the same.
+struct ReqPlan {
+    int q0, n, L, tiles, steps;   // steps: 64-key steps of its keys; 0 with no tiles
+    bool bad;
+};
+__device__ __forceinline__ ReqPlan plan_request(const PrefillArgs& a, int b) {
+    ReqPlan r;
+    r.q0 = a.q_start[b];
+    r.n = a.q_start[b + 1] - r.q0;
+    r.L = a.seq_lens[b];
+    r.bad = r.n < 0 || r.n > r.L || (int64_t)r.L > (int64_t)a.max_pages * kPage;
+    r.tiles = r.bad ? 0 : (int)(((int64_t)r.n * a.G + kPrefillRows - 1) / kPrefillRows);
+    r.steps = r.tiles > 0 ? (r.L + kPrefillKeys - 1) / kPrefillKeys : 0;
+    return r;
 }
 
-// pages of request b whose values the attention reads: all ceil(L_b / 16)
-// when it has query tiles, none otherwise
-__device__ __forceinline__ int vpages_of(const PrefillArgs& a, int b) {
-    return tiles_of(a, b) > 0 ? (a.seq_lens[b] + kPage - 1) / kPage : 0;
+// Inclusive scan over the wave's lanes (lane 63: the sum).
+__device__ __forceinline__ int lane_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr 1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true);   // row_bcast 15 into rows 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true);   // row_bcast 31 into rows 2, 3
+    return v;
 }
+__device__ __forceinline__ int lane_sum(int v) { return __builtin_amdgcn_readlane(lane_scan(v), 63); }
+
+// The plan of a batch of at most 64 requests, a request a lane.
+struct WavePlan {
+    ReqPlan r;
+    int S;          // units a tile
+    int u_end;      // inclusive scan of the requests' units per KV head
+    int units;      // units per KV head
+    __device__ __forceinline__ WavePlan(const PrefillArgs& a) {
+        const int lane = threadIdx.x & 63;
+        r = ReqPlan{0, 0, 0, 0, 0, false};
+        if (lane < a.B) r = plan_request(a, lane);
+        const int first = __builtin_amdgcn_readlane(r.q0, 0);
+        const int last = __builtin_amdgcn_readlane(r.q0 + r.n, a.B - 1);
+        const bool malformed = first < 0 || last > a.T || __ballot(r.n < 0) != 0;
+        if (blockIdx.x == 0 && threadIdx.x < 64 && (malformed || __ballot(r.bad) != 0) && lane == 0)
+            atomicOr(a.err, kErrLength);
+        if (malformed) r.tiles = r.steps = 0;
+        S = 1;
+        if (a.split) {
+            // the smallest chunk of C steps at which the units still run in
+            // as few rounds as the tiles do (see the host's rule)
+            const int items = lane_sum(r.tiles) * a.H_kv;
+            const int target = items <= a.slots / 4 ? a.slots / 2 : (items + a.slots - 1) / a.slots * a.slots;
+            int lo = kMinChunk, hi = 1;
+            {
+                int mx = r.steps;
+#pragma unroll
+                for (int o = 32; o >= 1; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 64));
+                hi = max(__builtin_amdgcn_readfirstlane(mx), lo);
+            }
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (lane_sum(r.tiles * ((r.steps + mid - 1) / mid)) * a.H_kv <= target) hi = mid;
+                else lo = mid + 1;
+            }
+            S = max((r.steps + lo - 1) / lo, 1);
+        }
+        u_end = lane_scan(r.tiles * S);
+        units = __builtin_amdgcn_readlane(u_end, 63);
+    }
+};
 
 __global__ void __launch_bounds__(kPlanThreads) prefill_plan_kernel(PrefillArgs a) {
     __shared__ int part[kPlanThreads];
     __shared__ int malformed;
-    __shared__ int total_pages;
+    __shared__ int total_steps;
     const int tid = threadIdx.x;
     if (tid == 0) malformed = (a.q_start[0] < 0 || a.q_start[a.B] > a.T) ? 1 : 0;
     __syncthreads();
@@ -225,42 +300,42 @@ __global__ void __launch_bounds__(kPlanThreads) prefill_plan_kernel(PrefillArgs 
     for (int k = 0; k < per; ++k) {
         const int b = b0 + k;
         if (b >= a.B) break;
-        if (a.q_start[b + 1] < a.q_start[b]) atomicOr(&malformed, 1);
-        const int t = tiles_of(a, b);
-        if (t < 0) bad = 1;
-        else sum += t;
+        const ReqPlan r = plan_request(a, b);
+        if (r.n < 0) atomicOr(&malformed, 1);
+        if (r.bad) bad = 1;
+        sum += r.tiles;
     }
     if (bad) atomicOr(a.err, kErrLength);
     const int incl = block_scan(sum, part);
     if (!a.fp8) {
-        // bf16 pools: the pages the value copy holds (every page of a request
+        // bf16 pools: the steps the value copy holds (every step of a request
         // with query tiles, none of the others; none at all when malformed)
-        int pages = 0;
+        int steps = 0;
         for (int k = 0; k < per; ++k)
-            if (b0 + k < a.B && !malformed) pages += vpages_of(a, b0 + k);
-        const int pincl = block_scan(pages, part);
-        int prun = pincl - pages;
+            if (b0 + k < a.B && !malformed) steps += plan_request(a, b0 + k).steps;
+        const int sincl = block_scan(steps, part);
+        int srun = sincl - steps;
         for (int k = 0; k < per; ++k) {
             const int b = b0 + k;
             if (b < a.B) {
-                a.page_off[b] = prun;
-                prun += malformed ? 0 : vpages_of(a, b);
+                a.step_off[b] = srun;
+                srun += malformed ? 0 : plan_request(a, b).steps;
             }
         }
         if (tid == kPlanThreads - 1) {
-            a.page_off[a.B] = pincl;
-            total_pages = pincl;
+            a.step_off[a.B] = sincl;
+            total_steps = sincl;
         }
-        __syncthreads();   // page_off is read back below by every thread
-        // the request of every copied page: the last b with page_off[b] <= p
-        for (int p = tid; p < total_pages; p += kPlanThreads) {
+        __syncthreads();   // step_off is read back below by every thread
+        // the request of every copied step: the last b with step_off[b] <= p
+        for (int p = tid; p < total_steps; p += kPlanThreads) {
             int lo = 0, hi = a.B - 1;
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
-                if (a.page_off[mid] <= p) lo = mid;
+                if (a.step_off[mid] <= p) lo = mid;
                 else hi = mid - 1;
             }
-            a.page_req[p] = lo;
+            a.step_req[p] = lo;
         }
     }
     if (malformed) {
@@ -277,7 +352,7 @@ __global__ void __launch_bounds__(kPlanThreads) prefill_plan_kernel(PrefillArgs 
         const int b = b0 + k;
         if (b < a.B) {
             a.tile_start[b] = run;
-            run += max(tiles_of(a, b), 0);
+            run += plan_request(a, b).tiles;
         }
     }
     if (tid == kPlanThreads - 1) a.tile_start[a.B] = incl;
@@ -286,21 +361,23 @@ __global__ void __launch_bounds__(kPlanThreads) prefill_plan_kernel(PrefillArgs 
 // ------------------------------------------------ fp16 copy of bf16 values --
 // Over bf16 pools PV runs in fp16, in one pass (P, below 2^8, keeps 11
 // significant bits in fp16; rounded to bf16 once it would spend the bf16
-// error budget).  Each (request, KV head)'s values are copied into the
-// workspace as fp16 at a power-of-two scale 2^e that puts their largest
-// magnitude M in [2^14, 2^15): bf16's 8 significant bits fit fp16's 11, so
-// every value of at least M 2^-28 converts exactly and none overflows, and
-// the rest keep an absolute error below M 2^-40.  The copy keeps the pool's
-// page layout [page][D][16 slots], a request's pages consecutive from
-// page_off[b], slots past its length zero.  Three passes, none with
-// atomics: vmax_kernel takes the largest magnitude of every (page, head)
-// tile, vreduce_kernel M of every (request, KV head), and vcopy_kernel
-// writes the copy.
+// error budget).  The values of every (64-key step, KV head) are copied into
+// the workspace as fp16 at a power-of-two scale 2^e of their own that puts
+// their largest magnitude M in [2^14, 2^15): bf16's 8 significant bits fit
+// fp16's 11, so every value of at least M 2^-28 converts exactly and none
+// overflows, and the rest keep an absolute error below M 2^-40.  A step's
+// four pages [D][16 slots] are contiguous, a request's steps consecutive,
+// slots past its length zero.  A scale a step needs one pass over the values
+// (a scale a (request, head) took three: the maximum of every tile, of every
+// (request, head), then the copy; 33 against 18 us on 36k tokens of 8 heads);
+// the attention works the difference of two steps' scales into the weights.
+constexpr int kAnyExp = 1 << 20;   // the step's values are all zero: any scale holds
 
 // the scale exponent e for a largest magnitude whose float bits are mb
-// (e = 0 when every value is zero or the maximum is not finite)
+// (e = 0 when the maximum is not finite)
 __device__ __forceinline__ int vcopy_exp(uint32_t mb) {
-    if (mb == 0u || mb >= 0x7f800000u) return 0;
+    if (mb == 0u) return kAnyExp;
+    if (mb >= 0x7f800000u) return 0;
     const int E = max((int)(mb >> 23), 1);          // floor(log2 M) + 127
     return min(max(141 - E, -126), 126);
 }
@@ -308,105 +385,92 @@ __device__ __forceinline__ float pow2f(int e) {   // 2^e, -126 <= e <= 127
     return __uint_as_float((uint32_t)(e + 127) << 23);
 }
 
-// The copy passes run a fixed grid of waves over the flat (page, KV head)
-// tiles of all requests; page p of the copy belongs to request page_req[p]
-// (written by the planner).  Each lane takes 4 (D = 128) or 2 16-byte units
-// (8 slots of one dim row) of a tile, all loaded before any is used.
-template <int D>
-struct VTile {
-    static constexpr int U = 2 * D / 64;   // units per lane
-    int b, j, g, pg, L;
-    u32x4 w[U];
-    // load tile t (p = t / H_kv, g = t % H_kv); slots past the length read as 0
-    __device__ __forceinline__ void load(const PrefillArgs& a, int64_t t, int lane) {
-        const int64_t p = t / a.H_kv;
-        g = (int)(t % a.H_kv);
-        b = a.page_req[p];
-        j = (int)(p - a.page_off[b]);
-        L = a.seq_lens[b];
-        pg = a.block_table[(int64_t)b * a.bt_stride + j];
-        const bool ok = (unsigned)pg < (unsigned)a.num_pages;
-        const uint16_t* src = (const uint16_t*)a.v_pages + ((int64_t)(ok ? pg : 0) * a.H_kv + g) * (D * kPage);
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const int r = 64 * k + lane, s0 = 8 * (r & 1);
-            w[k] = (ok && L - kPage * j - s0 > 0) ? *(const u32x4*)(src + (r >> 1) * kPage + s0) : u32x4{0u, 0u, 0u, 0u};
-        }
-    }
-    // value i of unit k, 0 past the length
-    __device__ __forceinline__ float value(int k, int i, int lane) const {
-        const int r = 64 * k + lane, live = L - kPage * j - 8 * (r & 1);
-        const uint32_t bits = (i & 1) ? (w[k][i >> 1] & 0xffff0000u) : (w[k][i >> 1] << 16);
-        return i < live ? __uint_as_float(bits) : 0.f;
-    }
-};
-
-__device__ __forceinline__ int64_t vcopy_tiles(const PrefillArgs& a) {
-    return (int64_t)a.page_off[a.B] * a.H_kv;
-}
-
-// largest |v| of each (page, head) tile, in tmax[tile]
-template <int D>
-__global__ void __launch_bounds__(256) vmax_kernel(PrefillArgs a) {
-    const int lane = threadIdx.x & 63;
-    const int64_t waves = (int64_t)gridDim.x * 4, n = vcopy_tiles(a);
-    for (int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); t < n; t += waves) {
-        VTile<D> v;
-        v.load(a, t, lane);
-        float m = 0.f;
-#pragma unroll
-        for (int k = 0; k < VTile<D>::U; ++k)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(v.value(k, i, lane)));
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-        if (lane == 0) a.tmax[t] = m;
-    }
-}
-
-// one wave per (request, KV head): vmax = float bits of the largest tile
-// maximum over the request's pages (0 for a request without copied pages)
-__global__ void __launch_bounds__(256) vreduce_kernel(PrefillArgs a) {
-    const int lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= (int64_t)a.B * a.H_kv) return;
-    const int b = (int)(i / a.H_kv), g = (int)(i % a.H_kv);
-    const int p0 = a.page_off[b], np = a.page_off[b + 1] - p0;
-    float m = 0.f;
-    for (int j = lane; j < np; j += 64) m = fmaxf(m, a.tmax[((int64_t)p0 + j) * a.H_kv + g]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    if (lane == 0) a.vmax[i] = __float_as_uint(m);
-}
-
+// One (step, KV head) at a time per workgroup, wave w its page w; each lane
+// takes 4 (D = 128) or 2 16-byte units (8 slots of one dim row) of the page,
+// all loaded before any is used.  Bound by memory: V read once, the copy
+// written once.
 template <int D>
 __global__ void __launch_bounds__(256) vcopy_kernel(PrefillArgs a) {
+    constexpr int U = 2 * D / 64;   // units per lane
+    __shared__ float wmax[2][4];
     const int lane = threadIdx.x & 63;
-    const int64_t waves = (int64_t)gridDim.x * 4, n = vcopy_tiles(a);
-    for (int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); t < n; t += waves) {
-        VTile<D> v;
-        v.load(a, t, lane);
-        const float sc = pow2f(vcopy_exp(a.vmax[(int64_t)v.b * a.H_kv + v.g]));
-        uint16_t* dst = a.vcopy + t * (int64_t)(D * kPage);   // tile t = (page, head) of the copy
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool self = a.B <= 64;
+    int s_end = 0, total, Lb = 0;
+    if (self) {
+        const WavePlan p(a);
+        s_end = lane_scan(p.r.steps);
+        total = __builtin_amdgcn_readlane(s_end, 63);
+        s_end -= p.r.steps;         // first step of this lane's request
+        Lb = p.r.steps > 0 ? p.r.L : 0;
+    } else {
+        total = a.step_off[a.B];
+    }
+    int par = 0;
+    for (int64_t t = blockIdx.x; t < (int64_t)total * a.H_kv; t += gridDim.x, par ^= 1) {
+        const int p = (int)(t / a.H_kv), g = (int)(t % a.H_kv);
+        int b, j, L;
+        if (self) {
+            // the last request with steps that starts at or before p
+            const uint64_t m = __ballot(Lb > 0 && s_end <= p);
+            b = 63 - __clzll((long long)m);
+            j = p - __builtin_amdgcn_readlane(s_end, b);
+            L = __builtin_amdgcn_readlane(Lb, b);
+        } else {
+            b = a.step_req[p];
+            j = p - a.step_off[b];
+            L = a.seq_lens[b];
+        }
+        const int pi = (kPrefillKeys / kPage) * j + w;     // this wave's page of the request
+        const bool inside = kPage * (int64_t)pi < L;
+        const int pg = inside ? a.block_table[(int64_t)b * a.bt_stride + pi] : -1;
+        const bool ok = (unsigned)pg < (unsigned)a.num_pages;
+        const uint16_t* src = (const uint16_t*)a.v_pages + ((int64_t)(ok ? pg : 0) * a.H_kv + g) * (D * kPage);
+        u32x4 v[U];
 #pragma unroll
-        for (int k = 0; k < VTile<D>::U; ++k) {
-            const int r = 64 * k + lane;
+        for (int k = 0; k < U; ++k) {
+            const int r = 64 * k + lane, live = L - kPage * pi - 8 * (r & 1);   // slots below the length
+            v[k] = ok && live > 0 ? *(const u32x4*)(src + (r >> 1) * kPage + 8 * (r & 1)) : u32x4{0u, 0u, 0u, 0u};
+            if (live < 8) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    v[k][i] &= (2 * i + 1 < live ? 0xffffffffu : 2 * i < live ? 0x0000ffffu : 0u);
+            }
+        }
+        float m = 0.f;
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                m = fmaxf(m, fmaxf(fabsf(__uint_as_float(v[k][i] << 16)), fabsf(__uint_as_float(v[k][i] & 0xffff0000u))));
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+        if (lane == 0) wmax[par][w] = m;
+        __syncthreads();            // two sets in turn: the next step's writes cannot pass this step's reads
+        m = fmaxf(fmaxf(wmax[par][0], wmax[par][1]), fmaxf(wmax[par][2], wmax[par][3]));
+        const int e = vcopy_exp(__float_as_uint(m));
+        if (threadIdx.x == 0) a.vexp[t] = e;
+        const float sc = e == kAnyExp ? 1.f : pow2f(e);
+        uint16_t* dst = a.vcopy + (t * (kPrefillKeys / kPage) + w) * (int64_t)(D * kPage);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
             u32x4 h;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const f32x2 x = {v.value(k, 2 * i, lane) * sc, v.value(k, 2 * i + 1, lane) * sc};
+                const f32x2 x = {__uint_as_float(v[k][i] << 16) * sc, __uint_as_float(v[k][i] & 0xffff0000u) * sc};
                 h[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, f16x2));   // round to nearest even
             }
-            *(u32x4*)(dst + (r >> 1) * kPage + 8 * (r & 1)) = h;
+            *(u32x4*)(dst + (64 * k + lane) * 8) = h;
         }
     }
 }
 
 // -------------------------------------------------------------- attention --
-// Workgroup = 128 query rows of one request and one query head; wave w owns
-// rows 32w..32w+31.  Keys go by steps of 64 (four pages).  The step's K and V
-// tiles are copied from the pool straight into LDS (global_load_lds, 16 bytes
-// a lane) in the pool's own layout (K [page][D/8 chunks][16 slots][8],
+// Workgroup = a unit of the plan: 128 query rows of one request and KV head
+// over a range of its keys; wave w owns rows 32w..32w+31.  Keys go by steps
+// of 64 (four pages).  The step's K and V tiles are copied from the pool
+// (bf16 pools: V from its fp16 copy) straight into LDS (global_load_lds, 16
+// bytes a lane) in the pool's own layout (K [page][D/8 chunks][16 slots][8],
 // V [page][D][16 slots], both XOR-swizzled against bank conflicts by the
 // choice of unit each lane fetches), double-buffered in four separate arrays
 // (so no read of one buffer waits on a copy into another), with K one step
@@ -421,15 +485,16 @@ __global__ void __launch_bounds__(256) vcopy_kernel(PrefillArgs a) {
 // O^T += V^T P^T for the 16 keys of page u, whose V^T elements are one
 // 16-byte run of each dim-major V row.  Online softmax in base 2 with a lazy
 // max: O and l are rescaled only when some column's max grows by more than
-// 2^8, so P stays below 2^8.  P enters as bf16 (hi) plus the bf16 remainder
-// (lo), carrying it to ~2^-17: P rounded to bf16 once would add up to 2^-9
-// of every weight on top of the output's own 2^-9 rounding, more than the
-// bf16 error budget allows.
+// 2^8, so P stays below 2^8.  P enters as fp16, rounded once (2^-12 of each
+// weight, against the output's own 2^-9).
 //
 // The loop is software-pipelined: step s masks and takes the max of S(s)
 // (computed one step earlier), then issues the MFMAs of S(s + 1)
 // interleaved with the exponentials of P(s), then the PV MFMAs of step s.
 constexpr float kLazyMax = 8.0f;
+// bf16 pools: a step's scale may be 2^7 coarser than the reference (P, below
+// 2^8, times 2^7 stays inside fp16) or 2^20 finer
+constexpr int kMaxCoarser = 7, kMaxFiner = 20;
 constexpr int kPageWindow = 1024;   // block-table entries staged in LDS
 constexpr int kXcds = 8;            // accelerator complexes; workgroup i runs on XCD i % 8
 // VALU instructions of the softmax placed between consecutive S MFMAs
@@ -474,45 +539,76 @@ prefill_attn_kernel(PrefillArgs a) {
     __shared__ __attribute__((aligned(16))) uint16_t vb0[KTW];
     __shared__ __attribute__((aligned(16))) uint16_t vb1[KTW];
     __shared__ int pages[kPageWindow];
+    __shared__ int vexps[FP8 ? 1 : WIN];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 31, hl = lane >> 5;
-    // work item r = ((g * tiles) + i) * G + j: KV head g, the i-th tile from
-    // the end (the longest first), query head g G + j.  Each of the 8 XCDs
-    // (workgroups go to XCD blockIdx % 8) takes a contiguous share of the
-    // items, so the G query heads and the neighbouring tiles that stream the
-    // same keys and values run together and share that XCD's L2.
-    const int tiles = a.tile_start[a.B];
-    const int items = tiles * a.H_q;
-    const int share = (items + kXcds - 1) / kXcds;
-    const int kq = (int)blockIdx.x / kXcds;
-    const int r = ((int)blockIdx.x % kXcds) * share + kq;
-    if (kq >= share || r >= items) return;
-    const int g = r / (tiles * a.G);
-    const int x = tiles - 1 - (r % (tiles * a.G)) / a.G;
-    const int h = g * a.G + r % a.G;
-    int lo = 0, hi = a.B - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (a.tile_start[mid] <= x) lo = mid;
-        else hi = mid - 1;
+    // work item r = g * units + i: KV head g, its i-th unit from the end (the
+    // longest first).  Each of the 8 XCDs (workgroups go to XCD blockIdx % 8)
+    // takes a contiguous share of the items, so the neighbouring tiles that
+    // stream the same keys and values run together and share that XCD's L2.
+    int units, b = 0, u0 = 0, S = 1, vstep0 = 0;
+    ReqPlan rq;
+    const int kq = (int)blockIdx.x / kXcds, xcd = (int)blockIdx.x % kXcds;
+    int r, g;
+    if (a.B <= 64) {
+        const WavePlan p(a);
+        units = p.units;
+        const int items = units * a.H_kv, share = (items + kXcds - 1) / kXcds;
+        r = xcd * share + kq;
+        if (kq >= share || r >= items) return;
+        g = r / units;
+        const int x = units - 1 - (r - g * units);
+        const int mine = p.r.tiles * p.S;
+        b = __ffsll((unsigned long long)__ballot(x < p.u_end)) - 1;    // the first whose units end past x
+        u0 = x - (__builtin_amdgcn_readlane(p.u_end, b) - __builtin_amdgcn_readlane(mine, b));
+        S = __builtin_amdgcn_readlane(p.S, b);
+        rq.q0 = __builtin_amdgcn_readlane(p.r.q0, b);
+        rq.n = __builtin_amdgcn_readlane(p.r.n, b);
+        rq.L = __builtin_amdgcn_readlane(p.r.L, b);
+        rq.tiles = __builtin_amdgcn_readlane(p.r.tiles, b);
+        if (!FP8) vstep0 = __builtin_amdgcn_readlane(lane_scan(p.r.steps) - p.r.steps, b);
+    } else {
+        units = a.tile_start[a.B];
+        const int items = units * a.H_kv, share = (items + kXcds - 1) / kXcds;
+        r = xcd * share + kq;
+        if (kq >= share || r >= items) return;
+        g = r / units;
+        const int x = units - 1 - (r - g * units);
+        int lo = 0, hi = a.B - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (a.tile_start[mid] <= x) lo = mid;
+            else hi = mid - 1;
+        }
+        b = lo;
+        rq = plan_request(a, b);
+        u0 = x - a.tile_start[b];
+        if (!FP8) vstep0 = a.step_off[b];
     }
-    const int b = lo;
-    const int t0 = a.q_start[b];
-    const int n = a.q_start[b + 1] - t0;
-    const int L = a.seq_lens[b];
+    const int chunk = u0 / rq.tiles, tile = u0 - chunk * rq.tiles;
+    const int t0 = rq.q0, n = rq.n, L = rq.L;
     const int p0 = L - n;                          // position of query token 0
-    const int r0 = (x - a.tile_start[b]) * kPrefillRows;
-    const int kv_end = p0 + min(r0 + kPrefillRows, n);   // keys [0, kv_end)
+    // rows tile 128 .. of the request's n G: the tile's first token and head
+    const int64_t rows_b = (int64_t)n * a.G, row_t = (int64_t)tile * kPrefillRows;
+    const int rows = (int)min(rows_b - row_t, (int64_t)kPrefillRows);
+    const int tok0 = (int)(row_t / a.G), head0 = (int)(row_t - (int64_t)tok0 * a.G);
+    auto token_of = [&](int i) { return tok0 + (int)((unsigned)(head0 + i) / (unsigned)a.G); };
+    const int kv_end = p0 + token_of(rows - 1) + 1;   // the tile's keys [0, kv_end)
     const int nsteps = (kv_end + KS - 1) / KS;
+    // this unit's steps
+    const int s_lo = (int)((int64_t)nsteps * chunk / S), s_hi = (int)((int64_t)nsteps * (chunk + 1) / S);
     const int np = (L + kPage - 1) / kPage;
     const int32_t* bt = a.block_table + (int64_t)b * a.bt_stride;
 
-    const int rw = r0 + 32 * w;                    // this wave's first row
-    const int row = min(rw + c, n - 1);            // padding columns repeat the last row
-    const int pos = p0 + row;                      // keys 0..pos are visible to this column
-    const int wave_steps = rw < n ? (p0 + min(rw + 31, n - 1)) / KS + 1 : 0;
+    const int rw = 32 * w;                         // this wave's first row of the tile
+    const int row = min(rw + c, rows - 1);         // padding columns repeat the last row
+    const int tok = token_of(row);
+    const int h = g * a.G + (head0 + row) - (tok - tok0) * a.G;
+    const int pos = p0 + tok;                      // keys 0..pos are visible to this column
+    const int pos_w = p0 + token_of(min(rw, rows - 1));   // the wave's first position
+    const int wave_steps = rw < rows ? min((p0 + token_of(min(rw + 31, rows - 1))) / KS + 1, s_hi) : 0;
 
     // softmax(scale * s) = softmax(|scale| * (-s)): for a negative scale the
     // query's sign bits are flipped (the host keeps |scale| >= FLT_MIN).
@@ -527,7 +623,7 @@ prefill_attn_kernel(PrefillArgs a) {
     {
         const uint32_t flip = s_eff < 0.f ? 0x80008000u : 0u;
         // the B operand of MFMA kb: dims 16 kb + 8 hl (fp8: 32 (kb / 2) + 16 hl + 8 (kb % 2))
-        const uint16_t* qrow = a.q + (int64_t)(t0 + row) * a.q_st + (int64_t)h * a.q_sh + (FP8 ? 16 : 8) * hl;
+        const uint16_t* qrow = a.q + (int64_t)(t0 + tok) * a.q_st + (int64_t)h * a.q_sh + (FP8 ? 16 : 8) * hl;
 #pragma unroll
         for (int kb = 0; kb < D / 16; ++kb) {
             u32x4 v = *(const u32x4*)(qrow + (FP8 ? 32 * (kb >> 1) + 8 * (kb & 1) : 16 * kb));
@@ -541,10 +637,15 @@ prefill_attn_kernel(PrefillArgs a) {
     float m = -INFINITY, l = 0.f;
     bool bad = false;
 
-    // the block-table entries of WIN steps at a time sit in LDS, refilled when
-    // no copy is in flight, so a step's pages cost LDS reads only
+    // the block-table entries (and value scales) of WIN steps at a time sit in
+    // LDS, refilled when no copy is in flight, so a step's pages cost LDS
+    // reads only; j a multiple of WIN
     auto refill = [&](int j) {
-        for (int e = tid; e < kPageWindow; e += 256) pages[e] = bt[min(PPS * j + e, np - 1)];
+        const int e1 = min(kPageWindow, PPS * (s_hi - j));   // entries the unit reads
+        for (int e = tid; e < e1; e += 256) pages[e] = bt[min(PPS * j + e, np - 1)];
+        if constexpr (!FP8)
+            for (int e = tid; e < min(WIN, s_hi - j); e += 256)
+                vexps[e] = a.vexp[(int64_t)(vstep0 + j + e) * a.H_kv + g];
         __syncthreads();
     };
     // unit u = 256 k + tid of a step: tensor u / (PPS UPP) (K, V), page
@@ -556,10 +657,9 @@ prefill_attn_kernel(PrefillArgs a) {
     const char* kbase = (const char*)a.k_pages + (int64_t)g * PB;
     const char* vbase = (const char*)a.v_pages + (int64_t)g * PB;
     const int64_t page_bytes = (int64_t)a.H_kv * PB;
-    // bf16 pools: the values come from the fp16 copy, whose pages of request
-    // b are consecutive from page_off[b] (same bytes per page as bf16)
-    const char* vbase16 = FP8 ? nullptr : (const char*)a.vcopy + (int64_t)g * PB;
-    const int64_t vpb = FP8 ? 0 : (int64_t)a.page_off[b];
+    // bf16 pools: the values come from the fp16 copy, whose steps of request b
+    // are consecutive from vstep0
+    const char* vbase16 = FP8 ? nullptr : (const char*)a.vcopy + ((int64_t)vstep0 * a.H_kv + g) * (PPS * PB);
     int64_t off1[PPS], off2[PPS];      // page byte offsets of steps s + 1 and s + 2
     auto pages_of = [&](int j, int64_t (&off)[PPS]) {
         const int e = PPS * (j % WIN);
@@ -611,36 +711,34 @@ prefill_attn_kernel(PrefillArgs a) {
             __builtin_amdgcn_global_load_lds(base + o_pg + vg * 16, dst + 8 * (256 * k + 64 * w), 16, 0, 0);
         }
     };
-    // the fp16 value copy of step j (bf16 pools), laid out and swizzled as V;
-    // a step past the request's pages re-reads its last page
+    // the fp16 value copy of step j (bf16 pools), laid out and swizzled as V
     auto dma_v16 = [&](int j, uint16_t* dst) {
+        const char* src = vbase16 + (int64_t)j * a.H_kv * (PPS * PB);
 #pragma unroll
         for (int k = 0; k < PERH; ++k) {
-            constexpr int BPP = 256 / UPP;
-            const int pp = (256 * k) / UPP + (BPP == 2 ? (w >> 1) : 0);
-            const int64_t o_pg = (vpb + min(PPS * j + pp, np - 1)) * page_bytes;
             const int v = ((256 * k + 64 * w) % UPP) + lane;
             const int vg = v ^ (((v >> 3) ^ (v >> 4)) & 1);
-            __builtin_amdgcn_global_load_lds(vbase16 + o_pg + vg * 16, dst + 8 * (256 * k + 64 * w), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(src + (256 * k + 64 * w - v + lane + vg) * 16, dst + 8 * (256 * k + 64 * w), 16,
+                                             0, 0);
         }
     };
-    // V slots of keys >= L hold no token (NaN in a pool); P is 0 there, and
-    // 0 * NaN must not reach O, so the tail step's slots are cleared
+    // a step whose values' scale is 2^d finer than the reference: its weights
+    // enter PV as 2^-d P (d <= kMaxFiner, where they are still normal numbers
+    // in the row sum; values finer than that give up the excess in LDS, at an
+    // absolute error far below the reference's)
+    auto coarsen = [&](uint16_t* V, int by) {
+        const _Float16 f = (_Float16)(by > 24 ? 0.f : pow2f(-by));
+        for (int e = tid; e < KT; e += 256) ((_Float16*)V)[e] *= f;
+    };
+    // fp8: V slots of keys >= L hold no token (NaN in a pool); P is 0 there,
+    // and 0 * NaN must not reach O, so the tail step's slots are cleared (the
+    // fp16 copy holds zeros there)
     auto clear_tail = [&](int s, uint16_t* V) {
-        if constexpr (FP8) {
-            // codes [page][D][16 slots], pages PBP bytes apart
-            uint8_t* Vb = (uint8_t*)V;
-            for (int e = tid; e < KT; e += 256) {
-                const int key = KS * s + 16 * (e / PE) + (e & 15);
-                if (key >= L) Vb[(e / PE) * PBP + e % PE] = 0;
-            }
-        } else {
-            for (int e = tid; e < KT; e += 256) {
-                const int d = (e % PE) >> 4;
-                const int half = ((e >> 3) & 1) ^ (((d >> 2) ^ (d >> 3)) & 1);
-                const int key = KS * s + 16 * (e / PE) + 8 * half + (e & 7);
-                if (key >= L) V[e] = 0;
-            }
+        // codes [page][D][16 slots], pages PBP bytes apart
+        uint8_t* Vb = (uint8_t*)V;
+        for (int e = tid; e < KT; e += 256) {
+            const int key = KS * s + 16 * (e / PE) + (e & 15);
+            if (key >= L) Vb[(e / PE) * PBP + e % PE] = 0;
         }
     };
 
@@ -714,35 +812,55 @@ prefill_attn_kernel(PrefillArgs a) {
         }
     };
 
-    // prologue: K and V of step 0, K of step 1, S of step 0
-    refill(0);
-    pages_of(0, off2);
-    dma(kbase, off2, kb0, false);
-    if constexpr (FP8) dma(vbase, off2, vb0, true);
-    else dma_v16(0, vb0);
-    if (nsteps > 1) {
-        pages_of(1, off1);
-        dma(kbase, off1, kb1, false);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (FP8 && KS > L) {   // (the fp16 copy holds zeros past the length)
-        clear_tail(0, vb0);
+    // bf16 pools: O is held at the scale 2^eref (kAnyExp while every value was
+    // zero), the same in all waves; a step whose values are at 2^(eref + d)
+    // takes its weights times 2^-d.  e1, e2: the scales of steps s, s + 1
+    // (before step s + 2's is read)
+    int eref = kAnyExp, e1 = kAnyExp, e2 = kAnyExp;
+    auto vexp_of = [&](int j) {
+        if constexpr (FP8) return 0;
+        else return __builtin_amdgcn_readfirstlane(vexps[j % WIN]);
+    };
+    auto finer = [&](int e) { return e == kAnyExp || eref == kAnyExp ? 0 : e - eref; };
+
+    // prologue: K and V of the first step, K of the next, S of the first
+    if (s_lo < s_hi) {
+        refill(s_lo / WIN * WIN);
+        pages_of(s_lo, off2);
+        e1 = vexp_of(s_lo);
+        dma(kbase, off2, kb0, false);
+        if constexpr (FP8) dma(vbase, off2, vb0, true);
+        else dma_v16(s_lo, vb0);
+        if (s_lo + 1 < s_hi) {
+            if ((s_lo + 1) % WIN == 0) {
+                __syncthreads();       // every wave has read the first step's pages
+                refill(s_lo + 1);
+            }
+            pages_of(s_lo + 1, off1);
+            e2 = vexp_of(s_lo + 1);
+            dma(kbase, off1, kb1, false);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
+        if (FP8 && KS * (s_lo + 1) > L) {
+            clear_tail(s_lo, vb0);
+            __syncthreads();
+        }
     }
     f32x16 sca[NH], scb[NH];
-    if (0 < wave_steps) qk(kb0, sca);
-    // step 0 copies K(2) over K(0): every wave's reads of K(0) come first
+    if (s_lo < wave_steps) qk(kb0, sca);
+    // the first step copies K(s + 2) over K(s): every wave's reads of it come first
     __syncthreads();
 
     // one step; sc holds S(s), scn receives S(s + 1)
     auto step = [&](auto par, const int s, f32x16 (&sc)[NH], f32x16 (&scn)[NH]) {
-        constexpr int P = decltype(par)::value;   // s % 2
+        constexpr int P = decltype(par)::value;   // (s - s_lo) % 2
         uint16_t* k_rd = P ? kb0 : kb1;   // K(s + 1)
         uint16_t* k_wr = P ? kb1 : kb0;   // K(s + 2), over K(s)
         uint16_t* v_rd = P ? vb1 : vb0;   // V(s)
         uint16_t* v_wr = P ? vb0 : vb1;   // V(s + 1), over V(s - 1)
-        const bool more_k = s + 2 < nsteps, more_v = s + 1 < nsteps;
+        const bool more_k = s + 2 < s_hi, more_v = s + 1 < s_hi;
+        int e3 = kAnyExp;
         if (more_v) {
             if constexpr (FP8) dma(vbase, off1, v_wr, true);
             else dma_v16(s + 1, v_wr);
@@ -750,13 +868,30 @@ prefill_attn_kernel(PrefillArgs a) {
         if (more_k) {
             if ((s + 2) % WIN == 0) refill(s + 2);
             pages_of(s + 2, off2);
+            e3 = vexp_of(s + 2);
             dma(kbase, off2, k_wr, false);
+        }
+        // the weights' factor 2^-d of this step, as the exponent's offset, and
+        // 2^d, which takes their sum back
+        float d = 0.f, pd = 1.f;
+        if constexpr (!FP8) {
+            if (eref == kAnyExp) eref = e1;        // O is zero so far
+            int di = min(finer(e1), kMaxFiner);
+            if (di < -kMaxCoarser) {               // values far larger than any before: O moves to their scale
+                const float f = di < -126 ? 0.f : pow2f(di);
+#pragma unroll
+                for (int t = 0; t < D / 32; ++t) o[t] *= f;
+                eref = e1;
+                di = 0;
+            }
+            d = (float)di;
+            pd = pow2f(di);
         }
         uint32_t ph[NH][8];   // P as fp16 pairs
         if (s < wave_steps) {
             // keys above a column's position are masked only on the steps
             // the wave's diagonal crosses
-            if (KS * s + KS - 1 > p0 + rw) {
+            if (KS * s + KS - 1 > pos_w) {
 #pragma unroll
                 for (int hh = 0; hh < NH; ++hh)
 #pragma unroll
@@ -783,16 +918,17 @@ prefill_attn_kernel(PrefillArgs a) {
             // (past a wave's last step the result is not used)
             qk(k_rd, scn);
             float psum = 0.f;
+            const float md = FP8 ? m : m + d;
 #pragma unroll
             for (int hh = 0; hh < NH; ++hh)
 #pragma unroll
                 for (int j = 0; j < 16; j += 2) {
-                    const f32x2 pq = {__builtin_amdgcn_exp2f(__builtin_fmaf(sc[hh][j], sl, -m)),
-                                      __builtin_amdgcn_exp2f(__builtin_fmaf(sc[hh][j + 1], sl, -m))};
+                    const f32x2 pq = {__builtin_amdgcn_exp2f(__builtin_fmaf(sc[hh][j], sl, -md)),
+                                      __builtin_amdgcn_exp2f(__builtin_fmaf(sc[hh][j + 1], sl, -md))};
                     psum += pq.x + pq.y;
                     ph[hh][j / 2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pq, f16x2));   // RNE
                 }
-            l += psum;
+            l = FP8 ? l + psum : __builtin_fmaf(psum, pd, l);
             // K reads run two MFMAs ahead of the S MFMAs, with the softmax
             // VALU work spread between them
             // (fp8: one K read per two MFMAs)
@@ -855,23 +991,44 @@ prefill_attn_kernel(PrefillArgs a) {
                 clear_tail(s + 1, v_wr);
                 __syncthreads();
             }
+            if (!FP8 && finer(e2) > kMaxFiner) {
+                coarsen(v_wr, finer(e2) - kMaxFiner);
+                __syncthreads();
+            }
         }
 #pragma unroll
         for (int q = 0; q < PPS; ++q) off1[q] = off2[q];
+        e1 = e2;
+        e2 = e3;
     };
     // unrolled by two so that S(s) and S(s + 1) alternate between register sets
-    for (int s = 0; s < nsteps; s += 2) {
+    for (int s = s_lo; s < s_hi; s += 2) {
         step(std::integral_constant<int, 0>{}, s, sca, scb);
-        if (s + 1 < nsteps) step(std::integral_constant<int, 1>{}, s + 1, scb, sca);
+        if (s + 1 < s_hi) step(std::integral_constant<int, 1>{}, s + 1, scb, sca);
     }
     if (bad && lane == 0) atomicOr(a.err, kErrPage);
-    if (rw >= n) return;
+    if (rw >= rows) return;
     const float l_tot = l + swap_halves(l);
-    // fp8: the V scale; bf16: undo the value copy's 2^e
-    if constexpr (!FP8) v_scale = pow2f(-vcopy_exp(a.vmax[(int64_t)b * a.H_kv + g]));
+    // fp8: the V scale; bf16: undo the values' scale
+    if constexpr (!FP8) v_scale = eref == kAnyExp ? 1.f : pow2f(-eref);
     const float f = v_scale / l_tot;
-    if (rw + c < n) {
-        uint16_t* orow = a.out + (int64_t)(t0 + rw + c) * a.o_st + (int64_t)h * a.o_sh;
+    if (S > 1) {
+        // a piece: its rows' (m, l) and normalised O, in the lanes' own order
+        // (dead, m = -inf, where the row sees no key of this unit)
+        const int64_t piece = (int64_t)r * 4 + w;
+        const bool dead = s_lo >= s_hi || pos < KS * s_lo;
+        if (hl == 0) a.part_ml[piece * 32 + c] = make_float2(dead ? -INFINITY : m, l_tot);
+        f32x4* po = (f32x4*)a.part_o + piece * (D / 8) * 64 + lane;
+#pragma unroll
+        for (int t = 0; t < D / 32; ++t)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4)
+                po[(4 * t + r4) * 64] = f32x4{o[t][4 * r4] * f, o[t][4 * r4 + 1] * f, o[t][4 * r4 + 2] * f,
+                                              o[t][4 * r4 + 3] * f};
+        return;
+    }
+    if (rw + c < rows) {
+        uint16_t* orow = a.out + (int64_t)(t0 + tok) * a.o_st + (int64_t)h * a.o_sh;
 #pragma unroll
         for (int t = 0; t < D / 32; ++t)
 #pragma unroll
@@ -883,6 +1040,81 @@ prefill_attn_kernel(PrefillArgs a) {
                 pk.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(v23, bf16x2));
                 *(u32x2*)(orow + 32 * t + 8 * r4 + 4 * hl) = pk;
             }
+    }
+}
+
+// Merge of the key-split tiles' pieces: a wave takes 32 dims (t) of 32 rows
+// (w) of a tile, in the lane order the attention kernel wrote them:
+//   M = max_i m_i,  out = sum_i 2^(m_i - M) l_i O_i / sum_i 2^(m_i - M) l_i
+// Bound by reading the pieces; every piece's loads are independent.
+template <int D>
+__global__ void __launch_bounds__(256) prefill_merge_kernel(PrefillArgs a) {
+    constexpr int NT = D / 32, WPT = 4 * NT;      // waves a tile
+    const int lane = threadIdx.x & 63, c = lane & 31, hl = lane >> 5;
+    const WavePlan p(a);
+    const int t_end = lane_scan(p.r.tiles);
+    const int tiles = __builtin_amdgcn_readlane(t_end, 63);
+    const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int item = __builtin_amdgcn_readfirstlane((int)(j / WPT)), q = __builtin_amdgcn_readfirstlane((int)(j % WPT));
+    if (tiles == 0 || item >= tiles * a.H_kv) return;
+    const int g = item / tiles, x = item - g * tiles;
+    const int b = __ffsll((unsigned long long)__ballot(x < t_end)) - 1;
+    const int S = __builtin_amdgcn_readlane(p.S, b);
+    if (S == 1) return;
+    const int tiles_b = __builtin_amdgcn_readlane(p.r.tiles, b), n = __builtin_amdgcn_readlane(p.r.n, b);
+    const int tile = x - (__builtin_amdgcn_readlane(t_end, b) - tiles_b);
+    const int u0 = __builtin_amdgcn_readlane(p.u_end, b) - tiles_b * S + tile;   // chunk k: u0 + k tiles_b
+    const int64_t row_t = (int64_t)tile * kPrefillRows;
+    const int rows = (int)min((int64_t)n * a.G - row_t, (int64_t)kPrefillRows);
+    const int w = q / NT, t = q - w * NT;
+    if (32 * w >= rows) return;
+    auto piece = [&](int k) { return ((int64_t)g * p.units + (p.units - 1 - (u0 + k * tiles_b))) * 4 + w; };
+    float M = -INFINITY, l = 0.f;
+    f32x4 acc[4] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f},
+                    f32x4{0.f, 0.f, 0.f, 0.f}};
+    constexpr int K = 4;                           // pieces a batch
+    for (int k0 = 0; k0 < S; k0 += K) {
+        float2 ml[K];
+        f32x4 o[K][4];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int64_t pc = piece(min(k0 + k, S - 1));
+            ml[k] = a.part_ml[pc * 32 + c];
+            if (k0 + k >= S) ml[k].x = -INFINITY;
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) o[k][r4] = *((const f32x4*)a.part_o + (pc * (D / 8) + 4 * t + r4) * 64 + lane);
+        }
+        float Mb = M;
+#pragma unroll
+        for (int k = 0; k < K; ++k) Mb = fmaxf(Mb, ml[k].x);
+        const float f = Mb > M ? __builtin_amdgcn_exp2f(M - Mb) : 1.f;
+        l *= f;
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) acc[r4] *= f;
+        M = Mb;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const bool live = ml[k].x != -INFINITY;
+            const float wt = live ? __builtin_amdgcn_exp2f(ml[k].x - M) * ml[k].y : 0.f;
+            l += wt;
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) acc[r4] += live ? wt * o[k][r4] : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    const int row = 32 * w + c;
+    if (row >= rows) return;
+    const float f = 1.f / l;
+    const int tok0 = (int)(row_t / a.G), head0 = (int)(row_t - (int64_t)tok0 * a.G);
+    const int dt = (int)((unsigned)(head0 + row) / (unsigned)a.G);
+    const int h = g * a.G + head0 + row - dt * a.G;
+    uint16_t* orow = a.out + (int64_t)(__builtin_amdgcn_readlane(p.r.q0, b) + tok0 + dt) * a.o_st + (int64_t)h * a.o_sh;
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+        const f32x2 v01 = {acc[r4][0] * f, acc[r4][1] * f}, v23 = {acc[r4][2] * f, acc[r4][3] * f};
+        u32x2 pk;
+        pk.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(v01, bf16x2));
+        pk.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(v23, bf16x2));
+        *(u32x2*)(orow + 32 * t + 8 * r4 + 4 * hl) = pk;
     }
 }
 
@@ -899,39 +1131,31 @@ void launch_kv_write(const WriteArgs& a, int32_t* page_start, hipStream_t s) {
     hipLaunchKernelGGL(lens_kernel, dim3((a.B + 255) / 256), dim3(256), 0, s, a);
 }
 
-constexpr int kHalves = 2;   // 32-key halves per step: 64 keys, four pages
 void launch_prefill_prep(const PrefillArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, a);
-    if (!a.fp8) {
-        const dim3 vgrid((unsigned)a.vgrid);
-        if (a.D == 128) {
-            hipLaunchKernelGGL(vmax_kernel<128>, vgrid, dim3(256), 0, s, a);
-        } else {
-            hipLaunchKernelGGL(vmax_kernel<64>, vgrid, dim3(256), 0, s, a);
-        }
-        hipLaunchKernelGGL(vreduce_kernel, dim3((unsigned)(((int64_t)a.B * a.H_kv + 3) / 4)), dim3(256), 0, s, a);
-        if (a.D == 128) {
-            hipLaunchKernelGGL(vcopy_kernel<128>, vgrid, dim3(256), 0, s, a);
-        } else {
-            hipLaunchKernelGGL(vcopy_kernel<64>, vgrid, dim3(256), 0, s, a);
-        }
-    }
+    if (a.B > 64) hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, a);
+    if (a.fp8) return;
+    if (a.D == 128) hipLaunchKernelGGL(vcopy_kernel<128>, dim3((unsigned)a.vgrid), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(vcopy_kernel<64>, dim3((unsigned)a.vgrid), dim3(256), 0, s, a);
 }
 
 void launch_prefill_attn(const PrefillArgs& a, hipStream_t s) {
-    // an upper bound on tiles x query heads, rounded up to whole XCD rows
-    const int64_t items = ((int64_t)(a.T + kPrefillRows - 1) / kPrefillRows + a.B) * a.H_q;
-    const dim3 grid((unsigned)((items + kXcds - 1) / kXcds * kXcds));
+    constexpr int NH = kPrefillKeys / 32;
+    const dim3 grid((unsigned)((a.max_units + kXcds - 1) / kXcds * kXcds));
     if (a.fp8) {
         if (a.D == 128)
-            hipLaunchKernelGGL((prefill_attn_kernel<128, kHalves, true>), grid, dim3(256), 0, s, a);
+            hipLaunchKernelGGL((prefill_attn_kernel<128, NH, true>), grid, dim3(256), 0, s, a);
         else
-            hipLaunchKernelGGL((prefill_attn_kernel<64, kHalves, true>), grid, dim3(256), 0, s, a);
+            hipLaunchKernelGGL((prefill_attn_kernel<64, NH, true>), grid, dim3(256), 0, s, a);
     } else if (a.D == 128) {
-        hipLaunchKernelGGL((prefill_attn_kernel<128, kHalves, false>), grid, dim3(256), 0, s, a);
+        hipLaunchKernelGGL((prefill_attn_kernel<128, NH, false>), grid, dim3(256), 0, s, a);
     } else {
-        hipLaunchKernelGGL((prefill_attn_kernel<64, kHalves, false>), grid, dim3(256), 0, s, a);
+        hipLaunchKernelGGL((prefill_attn_kernel<64, NH, false>), grid, dim3(256), 0, s, a);
     }
+    if (!a.split) return;
+    // a wave for every 32 rows x 32 dims of a tile
+    const dim3 mgrid((unsigned)(a.max_tiles * (a.D / 32)));
+    if (a.D == 128) hipLaunchKernelGGL(prefill_merge_kernel<128>, mgrid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(prefill_merge_kernel<64>, mgrid, dim3(256), 0, s, a);
 }
 
 }  // namespace bellman

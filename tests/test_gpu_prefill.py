@@ -186,6 +186,56 @@ def test_prefill_value_magnitudes():
     assert_close(got / per_head, ref / per_head, "bf16", "per-head magnitudes")
 
 
+def test_prefill_value_magnitudes_by_step():
+    # values whose magnitude changes from one 64-key step to the next (far up,
+    # far down, zeros, a little of both): each step of the fp16 value copy has
+    # a scale of its own, and the weights carry the difference.  A row's error
+    # is its output's bf16 rounding (2^-9 of each element at most) and its
+    # weights' fp16 rounding (2^-12), both relative to the row: 2.5e-3
+    exps = [None, -100, -100, -40, None, 16, 9, 14, -110, 16, 17, 60, None, 55, 61, -20]
+    H_q, H_kv, D = 4, 2, 64
+    w = wl.build_prefill(cached=[0, 0], new=[64 * len(exps), 700], H_q=H_q, H_kv=H_kv, D=D, seed=8, device="cuda")
+    fac = torch.tensor([0.0 if e is None else 2.0 ** e for e in exps], dtype=torch.float64, device="cuda")
+    pos = torch.cat([torch.arange(n, device="cuda") for n in (64 * len(exps), 700)])
+    w.v_new.copy_((w.v_new.double() * fac[pos // 64][:, None, None]).to(torch.bfloat16))
+    _write(w)
+    out = torch.full((w.T, H_q, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    _attend(w, w.q, out)
+    assert bl.device_errors() == 0
+    kp, vp = _host_pools(w)
+    ref = _oracle_prefill(w, kp, vp)
+    got = _out_f64(out)
+    norm = np.linalg.norm(ref, axis=-1)
+    zero = norm == 0                                  # the first step's rows see zeros only
+    assert zero.any() and np.all(got[zero] == 0.0)
+    rel = np.linalg.norm(got - ref, axis=-1)[~zero] / norm[~zero]
+    assert np.all(np.isfinite(got)) and rel.max() <= 2.5e-3, rel.max()
+
+
+SPLIT_CASES = [
+    # name, cached, new, H_q, H_kv, D: few tiles, so that their keys are cut
+    ("one_token", [5000], [1], 4, 1, 128),
+    ("whole_prompt_short_tiles", [0], [700], 2, 1, 64),       # tiles of fewer steps than units
+    ("past_a_table_window", [17000, 30], [40, 200], 7, 1, 128),
+    ("unequal", [3000, 0, 900], [129, 5, 64], 8, 2, 128),
+    ("64_requests", [100 + 40 * i for i in range(64)], [1 + i % 9 for i in range(64)], 4, 1, 64),
+    ("65_requests", [100 + 40 * i for i in range(65)], [1 + i % 9 for i in range(65)], 4, 1, 64),   # planned apart
+]
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+@pytest.mark.parametrize("case", SPLIT_CASES, ids=[c[0] for c in SPLIT_CASES])
+def test_prefill_key_split(case, kv):
+    name, cached, new, H_q, H_kv, D = case
+    w = wl.build_prefill(cached=cached, new=new, H_q=H_q, H_kv=H_kv, D=D, seed=len(name), device="cuda", kv=kv)
+    _write(w)
+    out = torch.full((w.T, H_q, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    _attend(w, w.q, out)
+    assert bl.device_errors() == 0
+    kp, vp = _host_pools(w)
+    assert_close(_out_f64(out), _oracle_prefill(w, kp, vp), "bf16", f"{name} {kv}")
+
+
 def _sweep_counts(rng, B, edge):
     out = []
     for _ in range(B):
