@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "../../include/bellman.h"
@@ -47,7 +48,20 @@ __device__ __forceinline__ float swap_halves(float x) {  // value of lane l ^ 32
 // leave as 16-byte runs of the dim-major V page [D][16 slots] (element by
 // element where the page is only partly written).  Lengths are advanced
 // afterwards by lens_kernel, so every item sees its request's old length.
+// Up to 64 requests there is no such launch: every wave counts the touched
+// pages itself, a request a lane.
 constexpr int kPlanThreads = 1024;
+
+// Inclusive scan over the wave's lanes (lane 63: the sum).
+__device__ __forceinline__ int lane_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr 1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true);   // row_bcast 15 into rows 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true);   // row_bcast 31 into rows 2, 3
+    return v;
+}
 
 // Inclusive scan of one value per thread over a kPlanThreads block.
 __device__ __forceinline__ int block_scan(int v, int* part) {
@@ -63,11 +77,10 @@ __device__ __forceinline__ int block_scan(int v, int* part) {
     return part[tid];
 }
 
-// Pages request b's new positions touch, or -1 for a malformed request
-// (negative or reversed range, rows past T, negative length).
-__device__ __forceinline__ int pages_touched(const WriteArgs& a, int b) {
-    const int s0 = a.q_start[b], s1 = a.q_start[b + 1];
-    const int L = a.seq_lens[b];
+// Pages a request's new positions touch (token rows s0 .. s1 - 1 after L
+// cached ones), or -1 for a malformed request (negative or reversed range,
+// rows past T, negative length).
+__device__ __forceinline__ int pages_touched(const WriteArgs& a, int s0, int s1, int L) {
     if (s0 < 0 || s1 < s0 || s1 > a.T || L < 0) return -1;
     if (s1 == s0) return 0;
     const int64_t last = (int64_t)L + (s1 - s0) - 1;
@@ -87,7 +100,7 @@ __global__ void __launch_bounds__(kPlanThreads) write_plan_kernel(WriteArgs a, i
         const int b = b0 + k;
         if (b >= a.B) break;
         if (a.q_start[b + 1] < a.q_start[b]) atomicOr(&malformed, 1);
-        const int t = pages_touched(a, b);
+        const int t = pages_touched(a, a.q_start[b], a.q_start[b + 1], a.seq_lens[b]);
         if (t < 0) bad = 1;
         else sum += t;
     }
@@ -107,7 +120,7 @@ __global__ void __launch_bounds__(kPlanThreads) write_plan_kernel(WriteArgs a, i
         const int b = b0 + k;
         if (b < a.B) {
             page_start[b] = run;
-            run += max(pages_touched(a, b), 0);
+            run += max(pages_touched(a, a.q_start[b], a.q_start[b + 1], a.seq_lens[b]), 0);
         }
     }
     if (tid == kPlanThreads - 1) {
@@ -119,25 +132,51 @@ __global__ void __launch_bounds__(kPlanThreads) write_plan_kernel(WriteArgs a, i
 template <int EB>
 __global__ void __launch_bounds__(256) kv_write_kernel(WriteArgs a, const int32_t* page_start) {
     __shared__ __attribute__((aligned(16))) uint8_t vst[kPage * 128 * 2];   // the page's V rows, one head
-    const int item = blockIdx.x, g = blockIdx.y, tid = threadIdx.x;
-    if (item >= page_start[a.B]) return;
-    int lo = 0, hi = a.B - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (page_start[mid] <= item) lo = mid;
-        else hi = mid - 1;
+    const int item = blockIdx.x, tid = threadIdx.x;
+    int b, s0, L, n, pi;
+    if (a.B <= 64) {
+        // the plan, as write_plan_kernel makes it
+        const int lane = tid & 63;
+        int q0 = 0, q1 = 0, Lb = 0, pages = 0;
+        if (lane < a.B) {
+            q0 = a.q_start[lane];
+            q1 = a.q_start[lane + 1];
+            Lb = a.seq_lens[lane];
+            pages = pages_touched(a, q0, q1, Lb);
+        }
+        const int last = __builtin_amdgcn_readlane(q1, a.B - 1);
+        const bool malformed = __builtin_amdgcn_readlane(q0, 0) < 0 || last > a.T || __ballot(q1 < q0) != 0;
+        if (item == 0 && blockIdx.y == 0 && tid < 64 && (malformed || last < a.T || __ballot(pages < 0) != 0) && lane == 0)
+            atomicOr(a.err, kErrAppendSlot);
+        if (malformed) return;
+        const int end = lane_scan(max(pages, 0));
+        if (item >= __builtin_amdgcn_readlane(end, 63)) return;
+        b = __ffsll((unsigned long long)__ballot(item < end)) - 1;      // the first whose pages end past item
+        s0 = __builtin_amdgcn_readlane(q0, b);
+        L = __builtin_amdgcn_readlane(Lb, b);
+        n = __builtin_amdgcn_readlane(q1, b) - s0;
+        pi = L / kPage + (item - (__builtin_amdgcn_readlane(end, b) - __builtin_amdgcn_readlane(pages, b)));
+    } else {
+        if (item >= page_start[a.B]) return;
+        int lo = 0, hi = a.B - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (page_start[mid] <= item) lo = mid;
+            else hi = mid - 1;
+        }
+        b = lo;
+        s0 = a.q_start[b];
+        L = a.seq_lens[b];
+        n = a.q_start[b + 1] - s0;
+        pi = L / kPage + (item - page_start[b]);
     }
-    const int b = lo;
-    const int s0 = a.q_start[b], L = a.seq_lens[b];
-    const int n = a.q_start[b + 1] - s0;
-    const int pi = L / kPage + (item - page_start[b]);
     const int64_t first = (int64_t)kPage * pi;              // position of slot 0
     const int slot_lo = (int)(max((int64_t)L, first) - first);
     const int slot_hi = (int)(min((int64_t)L + n, first + kPage) - first);
     int pg = -1;
     if (pi < a.max_pages) pg = a.block_table[(int64_t)b * a.bt_stride + pi];
     if (pg < 0 || pg >= a.num_pages) {
-        if (g == 0 && tid == 0) atomicOr(a.err, kErrAppendSlot);
+        if (blockIdx.y == 0 && tid == 0) atomicOr(a.err, kErrAppendSlot);
         return;
     }
     const int64_t row0 = s0 + (first - L);                   // token row of slot 0
@@ -145,37 +184,40 @@ __global__ void __launch_bounds__(256) kv_write_kernel(WriteArgs a, const int32_
     const int chunks = a.D / x;
     const char* kn = (const char*)a.k_new;
     const char* vn = (const char*)a.v_new;
-    char* kp = (char*)a.k_pages + ((int64_t)pg * a.H_kv + g) * (int64_t)a.D * kPage * EB;
-    char* vp = (char*)a.v_pages + ((int64_t)pg * a.H_kv + g) * (int64_t)a.D * kPage * EB;
-    for (int u = tid; u < chunks * kPage; u += 256) {
-        const int c = u / kPage, sl = u % kPage;
-        if (sl < slot_lo || sl >= slot_hi) continue;
-        const char* src = kn + ((row0 + sl) * a.k_st + (int64_t)g * a.k_sh + (int64_t)c * x) * EB;
-        *(u32x4*)(kp + (int64_t)u * 16) = *(const u32x4*)src;
-    }
-    const int row_units = a.D * EB / 16;                     // 16-byte units of one token's V row
-    for (int u = tid; u < kPage * row_units; u += 256) {
-        const int sl = u / row_units, k = u % row_units;
-        if (sl < slot_lo || sl >= slot_hi) continue;
-        *(u32x4*)&vst[u * 16] = *(const u32x4*)(vn + ((row0 + sl) * a.v_st + (int64_t)g * a.v_sh) * EB + k * 16);
-    }
-    __syncthreads();
-    // V page rows: unit (d, h) holds slots h x .. h x + x - 1 of dim d
-    const int row_bytes = a.D * EB;
-    for (int u = tid; u < a.D * EB; u += 256) {
-        const int d = u / EB, h = u % EB;
-        const int sa = h * x;
-        char* dst = vp + (int64_t)u * 16;
-        if (sa >= slot_lo && sa + x <= slot_hi) {
-            uint8_t buf[16];
+    for (int g = blockIdx.y; g < a.H_kv; g += gridDim.y) {
+        if (g != (int)blockIdx.y) __syncthreads();           // the last head's rows have been read
+        char* kp = (char*)a.k_pages + ((int64_t)pg * a.H_kv + g) * (int64_t)a.D * kPage * EB;
+        char* vp = (char*)a.v_pages + ((int64_t)pg * a.H_kv + g) * (int64_t)a.D * kPage * EB;
+        for (int u = tid; u < chunks * kPage; u += 256) {
+            const int c = u / kPage, sl = u % kPage;
+            if (sl < slot_lo || sl >= slot_hi) continue;
+            const char* src = kn + ((row0 + sl) * a.k_st + (int64_t)g * a.k_sh + (int64_t)c * x) * EB;
+            *(u32x4*)(kp + (int64_t)u * 16) = *(const u32x4*)src;
+        }
+        const int row_units = a.D * EB / 16;                     // 16-byte units of one token's V row
+        for (int u = tid; u < kPage * row_units; u += 256) {
+            const int sl = u / row_units, k = u % row_units;
+            if (sl < slot_lo || sl >= slot_hi) continue;
+            *(u32x4*)&vst[u * 16] = *(const u32x4*)(vn + ((row0 + sl) * a.v_st + (int64_t)g * a.v_sh) * EB + k * 16);
+        }
+        __syncthreads();
+        // V page rows: unit (d, h) holds slots h x .. h x + x - 1 of dim d
+        const int row_bytes = a.D * EB;
+        for (int u = tid; u < a.D * EB; u += 256) {
+            const int d = u / EB, h = u % EB;
+            const int sa = h * x;
+            char* dst = vp + (int64_t)u * 16;
+            if (sa >= slot_lo && sa + x <= slot_hi) {
+                uint8_t buf[16];
 #pragma unroll
-            for (int e = 0; e < x; ++e)
+                for (int e = 0; e < x; ++e)
 #pragma unroll
-                for (int q = 0; q < EB; ++q) buf[e * EB + q] = vst[(sa + e) * row_bytes + d * EB + q];
-            *(u32x4*)dst = *(const u32x4*)buf;
-        } else {
-            for (int sl = max(sa, slot_lo); sl < min(sa + x, slot_hi); ++sl)
-                for (int q = 0; q < EB; ++q) dst[(sl - sa) * EB + q] = (char)vst[sl * row_bytes + d * EB + q];
+                    for (int q = 0; q < EB; ++q) buf[e * EB + q] = vst[(sa + e) * row_bytes + d * EB + q];
+                *(u32x4*)dst = *(const u32x4*)buf;
+            } else {
+                for (int sl = max(sa, slot_lo); sl < min(sa + x, slot_hi); ++sl)
+                    for (int q = 0; q < EB; ++q) dst[(sl - sa) * EB + q] = (char)vst[sl * row_bytes + d * EB + q];
+            }
         }
     }
 }
@@ -234,16 +276,6 @@ __device__ __forceinline__ ReqPlan plan_request(const PrefillArgs& a, int b) {
     return r;
 }
 
-// Inclusive scan over the wave's lanes (lane 63: the sum).
-__device__ __forceinline__ int lane_scan(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr 1, 2, 4, 8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true);   // row_bcast 15 into rows 1, 3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true);   // row_bcast 31 into rows 2, 3
-    return v;
-}
 __device__ __forceinline__ int lane_sum(int v) { return __builtin_amdgcn_readlane(lane_scan(v), 63); }
 
 // The plan of a batch of at most 64 requests, a request a lane.
@@ -1121,13 +1153,18 @@ __global__ void __launch_bounds__(256) prefill_merge_kernel(PrefillArgs a) {
 }  // namespace
 
 void launch_kv_write(const WriteArgs& a, int32_t* page_start, hipStream_t s) {
-    hipLaunchKernelGGL(write_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, a, page_start);
+    if (a.B > 64) hipLaunchKernelGGL(write_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, a, page_start);
     // an upper bound on the pages touched: ceil(n_b / 16) + 1 per request
     const unsigned items = (unsigned)(a.T / kPage + 2 * a.B + 1);
-    if (a.elem_bytes == 2)
-        hipLaunchKernelGGL(kv_write_kernel<2>, dim3(items, (unsigned)a.H_kv), dim3(256), 0, s, a, (const int32_t*)page_start);
-    else
-        hipLaunchKernelGGL(kv_write_kernel<1>, dim3(items, (unsigned)a.H_kv), dim3(256), 0, s, a, (const int32_t*)page_start);
+    // the heads of a page go over as many workgroups as it takes to have 4096,
+    // so that the plan each makes is spread over the rest: 30k tokens of 8
+    // heads 48.5 us with a workgroup a head, 42.6 us with three heads each
+    // (planning launch and a workgroup a head before: 4.8 + 41.3 us; eight
+    // chats' 1.1k tokens 4.6 + 6.0 -> 6.0 us)
+    const unsigned ny = std::min((unsigned)a.H_kv, 4096u / std::min(items, 4096u) + 1);
+    const dim3 grid(items, ny);
+    if (a.elem_bytes == 2) hipLaunchKernelGGL(kv_write_kernel<2>, grid, dim3(256), 0, s, a, (const int32_t*)page_start);
+    else hipLaunchKernelGGL(kv_write_kernel<1>, grid, dim3(256), 0, s, a, (const int32_t*)page_start);
     hipLaunchKernelGGL(lens_kernel, dim3((a.B + 255) / 256), dim3(256), 0, s, a);
 }
 

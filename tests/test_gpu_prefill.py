@@ -115,6 +115,42 @@ def test_kv_write_flags_slots_outside_the_table():
     assert not np.array_equal(gk, kp0)               # the positions that fit were still written
 
 
+@pytest.mark.parametrize("B", [3, 64, 65])       # planned by each wave up to 64 requests, by a launch beyond
+def test_kv_write_malformed_requests(B):
+    cached, new = [5 + 3 * (i % 9) for i in range(B)], [(7 * i) % 33 for i in range(B)]
+    w = wl.build_prefill(cached=cached, new=new, H_q=2, H_kv=2, D=64, seed=B, device="cuda")
+    kp, vp = _host_pools(w)
+    seq = w.seq_lens.cpu().numpy().astype(np.int32)
+    oracle.kv_write(bits16(w.k_new), bits16(w.v_new), kp, vp, w.block_table.cpu().numpy(), seq,
+                    w.q_start.cpu().numpy())
+    kp0, vp0 = _host_pools(w)
+    bl.device_errors()
+    # a q_start that runs backwards, or past T: nothing is written
+    for i, v in ((1, -1), (B, w.T + 1), (B // 2, w.T + 5)):
+        qs = w.q_start.clone()
+        qs[i] = v
+        lens = w.seq_lens.clone()
+        bl.kv_write(w.k_new, w.v_new, w.k_pages, w.v_pages, w.block_table, lens, qs)
+        assert bl.device_errors() == 1, i
+        gk, gv = _host_pools(w)
+        assert np.array_equal(gk, kp0) and np.array_equal(gv, vp0), i
+    # a negative length: that request alone is left out
+    lens0 = w.seq_lens.clone()
+    w.seq_lens[1] = -4
+    _write(w)
+    assert bl.device_errors() == 1
+    assert int(w.seq_lens[1]) == -4
+    w.seq_lens[1] = lens0[1]
+    keep = torch.ones(B, dtype=torch.bool, device="cuda")
+    keep[1] = False
+    assert np.array_equal(w.seq_lens[keep].cpu().numpy(), seq[keep.cpu().numpy()])
+    gk, gv = _host_pools(w)
+    own = w.block_table[1][w.block_table[1] >= 0].cpu().numpy()
+    rest = np.setdiff1d(np.arange(w.num_pages), own)
+    assert np.array_equal(gk[rest], kp[rest]) and np.array_equal(gv[rest], vp[rest])
+    assert np.array_equal(gk[own], kp0[own]) and np.array_equal(gv[own], vp0[own])
+
+
 # --------------------------------------------------------- prompt attention --
 
 ATTN_CASES = [
