@@ -5,6 +5,7 @@
 // (arXiv 2510.15330, Sec. 3) controls: every request attends its one new
 // query token over its own KV cache (prompt plus tokens generated so far).
 #include "internal.h"
+#include "wave_scan.h"
 #include "work_split.h"
 
 #include <math.h>
@@ -213,24 +214,14 @@ __global__ void __launch_bounds__(512) kv_append_kernel(AppendArgs a) {
 // whether it holds PP pages or the last few (its loads are issued for all PP
 // pages), so dealing steps rather than pages keeps the waves' times equal
 // when many requests end in a short step.  Requests are split only where a
-// wave boundary falls inside them, and always between steps.
-constexpr int kPlanPerLane = 16;                        // lengths per lane per load batch
-constexpr int kPlanBatch = kPlanPerLane * kWaveSize;   // 1024 requests
-
-__device__ __forceinline__ int wave_incl_scan(int v, int lane) {
-#pragma unroll
-    for (int o = 1; o < kWaveSize; o <<= 1) {
-        const int t = __shfl_up(v, o, kWaveSize);
-        if (lane >= o) v += t;
-    }
-    return v;
-}
-
-__device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-    for (int o = kWaveSize / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWaveSize);
-    return v;
-}
+// wave boundary falls inside them, and always between steps.  The plan is a
+// serial stretch ahead of every wave's first page load: reading and summing
+// the lengths takes 0.44 us and locating the first unit 0.7 us up to 64
+// requests (2.1 and 1.4 us with 16 requests a lane, a scan through lane
+// shuffles and 64-bit divisions), 2.6 and 2.7 us at 512 with two waves a
+// SIMD (5.7 and 3.0 us).
+constexpr int kPlanRows = 8;                       // rows of 64 requests held in registers at a time
+constexpr int kPlanBatch = kPlanRows * kWaveSize;  // 512 requests
 
 // ------------------------------------------------ partial attention (MFMA) --
 // Each wave walks its contiguous share of the planner's steps, a step being
@@ -894,22 +885,29 @@ attn_mfma_kernel(AttnArgs a) {
     };
 
     // This wave's range of the P units (see the work split above).  Lane l
-    // holds requests b0 + 16 l .. b0 + 16 l + 15 of each batch of lengths, so
-    // one scan over the lanes gives every lane's first unit.
+    // holds requests b0 + l, b0 + 64 + l, ... of each batch of lengths: as
+    // many loads as rows of 64 requests, all out at once, and the rows'
+    // first units by one scan each.
     const int maxL = a.max_pages * kPage;
-    int Lk[kPlanPerLane], uk[kPlanPerLane];
+    int Lk[kPlanRows], uk[kPlanRows];
     bool bad_len = false;
+    auto rows_of = [&](int b0) { return min(kPlanRows, (a.B - b0 + kWaveSize - 1) / kWaveSize); };
     auto load_lens = [&](int b0) -> int {   // this lane's units in the batch
+        const int rows = rows_of(b0);
+#pragma unroll
+        for (int k = 0; k < kPlanRows; ++k) {
+            if (k >= rows) break;
+            Lk[k] = a.seq_lens[min(b0 + kWaveSize * k + lane, a.B - 1)];
+        }
         int sum = 0;
 #pragma unroll
-        for (int k = 0; k < kPlanPerLane; ++k) {
-            const int b = b0 + kPlanPerLane * lane + k;
+        for (int k = 0; k < kPlanRows; ++k) {
+            if (k >= rows) break;
             // slots past the batch hold no request: length 0, no units
-            const int Ls = b < a.B ? a.seq_lens[b] : 0;
-            if (Ls < 0 || Ls > maxL) bad_len = true;
-            const int L = b < a.B ? attn_len<STEP>(a, Ls) : 0;
-            Lk[k] = L;
-            uk[k] = ((L + kPage - 1) / kPage + PP - 1) / PP * a.H_kv;
+            const bool in = b0 + kWaveSize * k + lane < a.B;
+            if (in && (Lk[k] < 0 || Lk[k] > maxL)) bad_len = true;
+            Lk[k] = in ? attn_len<STEP>(a, Lk[k]) : 0;
+            uk[k] = ((Lk[k] + kPage - 1) / kPage + PP - 1) / PP * a.H_kv;
             sum += uk[k];
         }
         return sum;
@@ -917,14 +915,17 @@ attn_mfma_kernel(AttnArgs a) {
     // Requests of length 0 attend nothing and get rows of zeros: request b's
     // rows are written by wave b mod W, all lanes together.
     auto zero_empty = [&](int b0) {
+        const int rows = rows_of(b0);
 #pragma unroll
-        for (int k = 0; k < kPlanPerLane; ++k) {
-            const int b = b0 + kPlanPerLane * lane + k;
-            uint64_t m = __ballot(b < a.B && Lk[k] == 0 && b % a.waves == w);
+        for (int k = 0; k < kPlanRows; ++k) {
+            if (k >= rows) break;
+            const int b = b0 + kWaveSize * k + lane;
+            const bool empty = b < a.B && Lk[k] == 0;
+            if (__ballot(empty) == 0) continue;
+            uint64_t m = __ballot(empty && b % a.waves == w);
             while (m) {
-                const int src = __ffsll((unsigned long long)m) - 1;
+                const int bz = b0 + kWaveSize * k + __ffsll((unsigned long long)m) - 1;
                 m &= m - 1;
-                const int bz = b0 + kPlanPerLane * src + k;
                 // each head row is D bf16 = D / 4 8-byte units (rows are 8-byte aligned)
                 for (int u = lane; u < a.H_q * (D / 4); u += kWaveSize) {
                     const int h = u / (D / 4), c = u - h * (D / 4);
@@ -935,12 +936,11 @@ attn_mfma_kernel(AttnArgs a) {
     };
     int lsum = load_lens(0);
     zero_empty(0);
-    int incl = wave_incl_scan(lsum, lane);
-    int P = __builtin_amdgcn_readlane(incl, kWaveSize - 1);
     for (int b0 = kPlanBatch; b0 < a.B; b0 += kPlanBatch) {
-        P += __builtin_amdgcn_readfirstlane(wave_sum(load_lens(b0)));
+        lsum += load_lens(b0);
         zero_empty(b0);
     }
+    const int P = __builtin_amdgcn_readlane(lane_scan(lsum), kWaveSize - 1);
     const int W = min(a.waves, P);     // no more waves than units take a share
     const int skew = share_skew(a.skew, P, W, PP);
     // wave 0 raises the length flag
@@ -956,36 +956,26 @@ attn_mfma_kernel(AttnArgs a) {
     }
     int sb = -1, sg = 0, sp = 0, sL = 0;   // request, KV head, page, length at unit r0
     int carry = 0;                         // units of the requests before this batch
-    for (int b0 = 0; b0 < a.B; b0 += kPlanBatch) {
-        if (b0 > 0) {
-            lsum = load_lens(b0);
-            incl = wave_incl_scan(lsum, lane);
-        } else if (a.B > kPlanBatch) {
-            lsum = load_lens(0);
-            incl = wave_incl_scan(lsum, lane);
-        }
-        const int excl = carry + incl - lsum;
-        const uint64_t hit = __ballot(lsum > 0 && excl <= r0 && r0 < excl + lsum);
-        if (sb < 0 && hit != 0) {
-            // walk the 16 requests of the lane that holds unit r0
-            const int src = __ffsll((unsigned long long)hit) - 1;
-            int x = __builtin_amdgcn_readlane(excl, src);
+    for (int b0 = 0; sb < 0 && b0 < a.B; b0 += kPlanBatch) {
+        if (a.B > kPlanBatch) load_lens(b0);
+        const int rows = rows_of(b0);
 #pragma unroll
-            for (int k = 0; k < kPlanPerLane; ++k) {
+        for (int k = 0; k < kPlanRows; ++k) {
+            if (k >= rows || sb >= 0) break;
+            const int incl = carry + lane_scan(uk[k]);
+            const uint64_t hit = __ballot(r0 < incl);      // the first request whose units end past r0
+            if (hit != 0) {
+                const int src = __ffsll((unsigned long long)hit) - 1;
                 const int u = __builtin_amdgcn_readlane(uk[k], src);
-                if (sb < 0 && r0 < x + u) {
-                    const int ns = u / a.H_kv;
-                    const int off = r0 - x;
-                    sb = b0 + kPlanPerLane * src + k;
-                    sL = __builtin_amdgcn_readlane(Lk[k], src);
-                    sg = off / ns;
-                    sp = off % ns * PP;
-                }
-                x += u;
+                const int off = r0 - (__builtin_amdgcn_readlane(incl, src) - u);
+                sb = b0 + kWaveSize * k + src;
+                sL = __builtin_amdgcn_readlane(Lk[k], src);
+                const int ns = ((sL + kPage - 1) / kPage + PP - 1) / PP;
+                sg = (int)((unsigned)off / (unsigned)ns);
+                sp = (off - sg * ns) * PP;
             }
+            carry = __builtin_amdgcn_readlane(incl, kWaveSize - 1);
         }
-        carry += __builtin_amdgcn_readlane(incl, kWaveSize - 1);
-        if (sb >= 0) break;
     }
 
     const size_t tile_bytes = (size_t)D * kPage * EB;

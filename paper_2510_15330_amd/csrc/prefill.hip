@@ -16,6 +16,7 @@
 
 #include "../../include/bellman.h"
 #include "internal.h"
+#include "wave_scan.h"
 
 namespace bellman {
 namespace {
@@ -51,17 +52,6 @@ __device__ __forceinline__ float swap_halves(float x) {  // value of lane l ^ 32
 // Up to 64 requests there is no such launch: every wave counts the touched
 // pages itself, a request a lane.
 constexpr int kPlanThreads = 1024;
-
-// Inclusive scan over the wave's lanes (lane 63: the sum).
-__device__ __forceinline__ int lane_scan(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr 1, 2, 4, 8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true);   // row_bcast 15 into rows 1, 3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true);   // row_bcast 31 into rows 2, 3
-    return v;
-}
 
 // Inclusive scan of one value per thread over a kPlanThreads block.
 __device__ __forceinline__ int block_scan(int v, int* part) {

@@ -377,6 +377,20 @@ def test_large_batches_of_short_requests(B, kv):
         assert np.all(got[lens == 0] == 0.0)
 
 
+@pytest.mark.parametrize("B", [63, 64, 65, 511, 512, 513, 1025])
+def test_batches_at_the_planner_row_edges(B):
+    # the planner holds 64 requests a row and 8 rows at a time
+    rng = np.random.default_rng(B)
+    lens = rng.integers(0, 50, size=B)
+    lens[[0, B // 2, B - 1]] = [0, 0, 33]
+    case = dn.random_case(rng, B, 4, 2, 64, [int(x) for x in lens], "bf16")
+    ref = oracle_case(case, 0.125)
+    for waves in (0, 3, 1000):
+        got = run_case(dev_case(case), 0.125, max_waves=waves)
+        G.assert_close(got, ref, "bf16", f"B={B} waves={waves}")
+        assert np.all(got[lens == 0] == 0.0)
+
+
 def test_fp8_every_code_through_single_token_rows():
     """Length-1 requests return their V row times the V scale; with scale 1 the
     output is the e4m3fn value itself, so every finite code is checked."""
