@@ -1,4 +1,9 @@
-"""ctypes binding of libbellman.so: argument marshalling only."""
+"""Binding of libbellman.so: argument marshalling only.
+
+The device calls go through the ``_marshal`` extension, which reads plain
+device tensors in native code; what it leaves (other types, host tensors)
+takes the ctypes path here, which raises the errors.  Everything else is
+ctypes."""
 from __future__ import annotations
 
 import ctypes
@@ -82,6 +87,11 @@ class LoadSignal(ctypes.Structure):
 
 
 _lib = None
+_native = None          # _marshal.call
+_addr = {}              # entry point -> its address, for _marshal.call
+
+# the forms of call (marshal.cpp)
+_APPEND, _DECODE, _DECODE_OPTS, _STEP, _WRITE, _PREFILL = range(6)
 
 
 def library_path() -> str:
@@ -90,9 +100,13 @@ def library_path() -> str:
 
 def library():
     """Load libbellman.so (built in-tree); raise if it is missing."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
+    try:
+        from . import _marshal
+    except ImportError as e:
+        raise RuntimeError(f"the _marshal extension is not built ({e}); run __graft_entry__.build() first") from e
     if not os.path.exists(_LIB_PATH):
         raise RuntimeError(f"{_LIB_PATH} is not built; run __graft_entry__.build() "
                            "(hipcc, gfx950) first — there is no fallback path")
@@ -150,6 +164,12 @@ def library():
     lib.bellman_shutdown.restype = None
     lib.bellman_version.argtypes = []
     lib.bellman_version.restype = ctypes.c_char_p
+    for name in ("kv_append", "decode_attention", "decode_attention_noalloc", "decode_step", "kv_write",
+                 "prefill_attention"):
+        _addr[name] = ctypes.cast(getattr(lib, "bellman_" + name), P).value
+    _marshal.setup(torch.Tensor, torch.nn.Parameter, tuple(_DTYPES.items()), torch.float32,
+                   torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+    _native = _marshal.call
     _lib = lib
     return lib
 
@@ -208,12 +228,29 @@ def _stream(stream):
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 
+def _call(name, form, stream, scale, opts, k_scale, v_scale, *tensors):
+    """The native path: True if it made the call, False if it is not a case
+    for it (nothing was done)."""
+    if _native is None:
+        library()
+    st = None if stream is None else _stream(stream).value or 0
+    rc = _native(_addr[name], form, st, scale, opts, k_scale, v_scale, *tensors)
+    if rc is None:
+        return False
+    if rc != 0:
+        raise BellmanError(rc, last_error())
+    return True
+
+
 def kv_append(k_new, v_new, k_pages, v_pages, block_table, seq_lens, stream=None,
               k_scale=None, v_scale=None):
     """bellman_kv_append: write one token per request, then seq_lens += 1.
 
     bf16 rows into fp8 pools are quantised with k_scale / v_scale (the
     pools' per-(request, KV head) dequantisation scales)."""
+    if _call("kv_append", _APPEND, stream, 0.0, 0, k_scale, v_scale, k_new, v_new, k_pages, v_pages, block_table,
+             seq_lens):
+        return
     _device_tensors(k_new, v_new, k_pages, v_pages, block_table, seq_lens, k_scale, v_scale)
     lib = library()
     _check(lib.bellman_kv_append(desc(k_new), desc(v_new), desc(k_pages, k_scale), desc(v_pages, v_scale),
@@ -230,6 +267,10 @@ def decode_attention(q, k_pages, v_pages, block_table, seq_lens, scale, out, str
     is 0 (the library's choice), -1 (equal shares) or 1..255; ``wave_times``
     an optional device int64 tensor of 3 entries per wave for the per-wave
     timing records."""
+    if (max_waves == 0 and xcd_skew == 0 and events is None and pages_per_step == 0 and pipeline_depth == 0
+            and wave_times is None and _call("decode_attention", _DECODE, stream, scale, 0, k_scale, v_scale, q,
+                                             k_pages, v_pages, block_table, seq_lens, out)):
+        return
     _device_tensors(q, k_pages, v_pages, block_table, seq_lens, out, k_scale, v_scale, wave_times)
     lib = library()
     args = (desc(q), desc(k_pages, k_scale), desc(v_pages, v_scale), desc(block_table),
@@ -253,8 +294,11 @@ def decode_attention_noalloc(q, k_pages, v_pages, block_table, seq_lens, scale, 
                              pipeline_depth=0):
     """bellman_decode_attention_noalloc: decode_attention with its scratch in
     the device's fixed array (no device allocation)."""
-    _device_tensors(q, k_pages, v_pages, block_table, seq_lens, out, k_scale, v_scale)
     opts = AttnOpts(int(max_waves), int(xcd_skew), int(pages_per_step), int(pipeline_depth), None, None)
+    if _call("decode_attention_noalloc", _DECODE_OPTS, stream, scale, ctypes.addressof(opts), k_scale, v_scale, q,
+             k_pages, v_pages, block_table, seq_lens, out):
+        return
+    _device_tensors(q, k_pages, v_pages, block_table, seq_lens, out, k_scale, v_scale)
     _check(library().bellman_decode_attention_noalloc(
         desc(q), desc(k_pages, k_scale), desc(v_pages, v_scale), desc(block_table), desc(seq_lens),
         ctypes.c_float(scale), desc(out), ctypes.byref(opts), _stream(stream)))
@@ -273,6 +317,9 @@ def decode_step(k_new, v_new, q, k_pages, v_pages, block_table, seq_lens, scale,
             raise ValueError("record each event once before passing it")
     wt = None if wave_times is None else wave_times.data_ptr()
     opts = AttnOpts(int(max_waves), int(xcd_skew), int(pages_per_step), int(pipeline_depth), ev0, ev1, wt)
+    if _call("decode_step", _STEP, stream, scale, ctypes.addressof(opts), k_scale, v_scale, k_new, v_new, q, k_pages,
+             v_pages, block_table, seq_lens, out):
+        return
     _check(library().bellman_decode_step(
         desc(k_new), desc(v_new), desc(q), desc(k_pages, k_scale), desc(v_pages, v_scale), desc(block_table),
         desc(seq_lens), ctypes.c_float(scale), desc(out), ctypes.byref(opts), _stream(stream)))
@@ -291,6 +338,9 @@ def probe_gather(pool, tile_bytes, sink, max_waves=0, stream=None):
 def kv_write(k_new, v_new, k_pages, v_pages, block_table, seq_lens, q_start, stream=None):
     """bellman_kv_write: write each request's new prompt tokens after its
     cached ones, then seq_lens += tokens written."""
+    if _call("kv_write", _WRITE, stream, 0.0, 0, None, None, k_new, v_new, k_pages, v_pages, block_table, seq_lens,
+             q_start):
+        return
     _device_tensors(k_new, v_new, k_pages, v_pages, block_table, seq_lens, q_start)
     _check(library().bellman_kv_write(desc(k_new), desc(v_new), desc(k_pages), desc(v_pages), desc(block_table),
                                       desc(seq_lens), desc(q_start), _stream(stream)))
@@ -301,6 +351,9 @@ def prefill_attention(q, k_pages, v_pages, block_table, seq_lens, q_start, scale
     """bellman_prefill_attention(_opts): causal attention of each request's
     new (last) tokens over its cached ones (fp8 pools with their
     per-(request, KV head) dequantisation scales k_scale / v_scale)."""
+    if events is None and _call("prefill_attention", _PREFILL, stream, scale, 0, k_scale, v_scale, q, k_pages,
+                                v_pages, block_table, seq_lens, q_start, out):
+        return
     _device_tensors(q, k_pages, v_pages, block_table, seq_lens, q_start, out, k_scale, v_scale)
     lib = library()
     args = (desc(q), desc(k_pages, k_scale), desc(v_pages, v_scale), desc(block_table), desc(seq_lens),

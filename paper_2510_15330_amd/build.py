@@ -1,4 +1,4 @@
-"""Build libbellman.so in-tree with hipcc for gfx950.
+"""Build libbellman.so (hipcc, gfx950) and the _marshal extension (g++) in-tree.
 
 ``python -m paper_2510_15330_amd.build --sanitize OUT.so`` builds the same
 library with the host code of its C++ sources (descriptor validation,
@@ -11,11 +11,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbellman.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")     # CPython extension, host only
 DEVICE_SOURCES = ["kernels.hip", "prefill.hip", "device_state.hip", "probe.hip"]
 HOST_SOURCES = ["bellman_api.cpp", "controller.cpp", "serve_sim.cpp"]
 SOURCES = DEVICE_SOURCES + HOST_SOURCES
@@ -43,7 +45,7 @@ def _run(cmd, verbose):
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({res.returncode}):\n{out}")
+        raise RuntimeError(f"{cmd[0]} failed ({res.returncode}):\n{out}")
     if verbose and out.strip():
         print(out)
 
@@ -68,7 +70,15 @@ def _build(out: str, sanitize: bool, verbose: bool) -> str:
     return out
 
 
+def _build_marshal(verbose: bool) -> None:
+    tmp = MARSHAL + f".tmp{os.getpid()}"
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
+          os.path.join(CSRC, "marshal.cpp"), "-o", tmp], verbose)
+    os.replace(tmp, MARSHAL)
+
+
 def build(verbose: bool = False) -> str:
+    _build_marshal(verbose)
     tmp = LIB + f".tmp{os.getpid()}"
     _build(tmp, False, verbose)
     os.replace(tmp, LIB)
