@@ -700,23 +700,25 @@ int bellman_prefill_attention_opts(const bellman_tensor_t* q, const bellman_tens
     // KV heads, and the attention workgroups resident at once (two a CU).
     // Where there may be too few tiles to keep those busy, a tile's keys are
     // cut as well, in units that still run in as many rounds as the tiles
-    // would (half a round, one a CU, where they are under a quarter of one).
-    // From two rounds on the hardware's own balance is left to do it (2048
-    // tiles, four rounds: the same uncut).  Letting 336 tiles take 1016 units
-    // instead of 488 ran the attention in 127 against 129 us and its merge in
-    // 17 against 11 us.
+    // would: 64 tiles of 108 steps on 512 units (14 steps each) took 41 us and
+    // 8 us of merge, on 256 units 50 and 6 us, uncut 141 us.  336 tiles on
+    // 1016 units instead of 488 ran in 127 against 129 us and their merge in
+    // 17 against 11 us.  From two rounds on the hardware's own balance is left
+    // to do it (2048 tiles, four rounds: the same uncut).  A table of no more
+    // keys than one unit takes is never cut, and needs no merge launch.
     PrefillArgs a;
     const int64_t rows = T * (H_q / ps.H_kv);
     a.max_tiles = (rows / kPrefillRows + B) * ps.H_kv;
     a.slots = 2 * g_cu_count[dev];
-    a.split = B <= 64 && a.max_tiles <= 2 * a.slots;
+    a.split = B <= 64 && a.max_tiles <= 2 * a.slots && max_pages * kPage > kPrefillMinChunk * kPrefillKeys;
     a.max_units = a.split ? (a.max_tiles + a.slots - 1) / a.slots * a.slots : a.max_tiles;
 
     const bool planned = B > 64;           // by a kernel of its own (each wave plans for itself up to 64)
     const size_t max_steps = (size_t)B * (size_t)((max_pages + 3) / 4);
     const size_t piece_rows = a.split ? (size_t)a.max_units * kPrefillRows : 0;
     const size_t off_tiles = kWsHeader;
-    const size_t off_ml = off_tiles + align256(planned ? (size_t)(B + 1) * 4 : 0);
+    const size_t off_chunk = off_tiles + align256(planned ? (size_t)(B + 1) * 4 : 0);
+    const size_t off_ml = off_chunk + 256;
     const size_t off_o = off_ml + align256(piece_rows * sizeof(float2));
     const size_t off_steps = off_o + align256(piece_rows * ps.D * sizeof(float));
     const size_t off_req = off_steps + align256(planned && !ps.fp8 ? (size_t)(B + 1) * 4 : 0);
@@ -758,6 +760,7 @@ int bellman_prefill_attention_opts(const bellman_tensor_t* q, const bellman_tens
     a.fp8 = ps.fp8 ? 1 : 0;
     a.k_scale = k_pages->dequant_scale;
     a.v_scale = v_pages->dequant_scale;
+    a.chunk = (int32_t*)(base + off_chunk);
     a.part_ml = (float2*)(base + off_ml);
     a.part_o = (float*)(base + off_o);
     a.step_off = (int32_t*)(base + off_steps);

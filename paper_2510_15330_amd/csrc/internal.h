@@ -105,6 +105,7 @@ struct WriteArgs {
 // Prompt (prefill) attention over the paged cache (prefill.hip).
 constexpr int kPrefillRows = 128;   // query rows per workgroup (4 waves x 32)
 constexpr int kPrefillKeys = 64;    // keys per step (four pages)
+constexpr int kPrefillMinChunk = 8; // steps a unit of a key-split tile takes at least
 struct PrefillArgs {
     const uint16_t* q;   // bf16 [T, H_q, D]
     int64_t q_st, q_sh;
@@ -129,6 +130,7 @@ struct PrefillArgs {
     int slots;             // attention workgroups the device holds at once
     // workspace
     int32_t* tile_start;   // [B + 1]: first query tile of each request (B > 64)
+    int32_t* chunk;        // steps of a key-split unit, written by the attention for the merge
     float2* part_ml;       // [max_units, 128]: (running max in log2 units, sum) of each row of a piece
     float* part_o;         // [max_units, 128 D]: its normalised output, in lane order
     // bf16 pools: the fp16 copy of the values the attention reads

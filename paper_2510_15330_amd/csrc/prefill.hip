@@ -227,7 +227,6 @@ __global__ void lens_kernel(WriteArgs a) {
 }
 
 // --------------------------------------------------------------- planning --
-constexpr int kMinChunk = 8;   // steps a unit of a key-split tile takes at least
 // A request's query rows are its n_b tokens x the G query heads of a KV
 // head, token-major (row r: token r / G, head r % G): tiles of 128 rows,
 // whose heads share the KV head's keys.  A request whose range is malformed
@@ -247,8 +246,8 @@ constexpr int kMinChunk = 8;   // steps a unit of a key-split tile takes at leas
 //
 // Measured, whole prompt steps, against rows of one query head each, no key
 // split and the planning launch: one 2048-token chunk after 4,900 tokens on
-// 4/2 heads (64 tiles: 256 units of 27 steps) 171 -> 70 us, the attention
-// alone 141 -> 49 us and 7 us of merge; eight chats' 16-256 new tokens after
+// 4/2 heads (64 tiles: 512 units of 14 steps) 171 -> 59 us, the attention
+// alone 141 -> 41 us and 8 us of merge (256 units: 50 + 6 us); eight chats' 16-256 new tokens after
 // 2-8k (336 tiles instead of 416, 488 units) 207 -> 172 us; four prompts of
 // 6-12k (7584 tiles, never cut) the same.
 struct ReqPlan {
@@ -274,7 +273,11 @@ struct WavePlan {
     int S;          // units a tile
     int u_end;      // inclusive scan of the requests' units per KV head
     int units;      // units per KV head
-    __device__ __forceinline__ WavePlan(const PrefillArgs& a) {
+    int chunk;      // steps of a key-split unit
+    // known: the chunk, 0 to find it (the merge reads what the attention
+    // found: the search is a third of its plan); without `cut` the units are
+    // not needed
+    __device__ __forceinline__ WavePlan(const PrefillArgs& a, bool cut, int known) {
         const int lane = threadIdx.x & 63;
         r = ReqPlan{0, 0, 0, 0, 0, false};
         if (lane < a.B) r = plan_request(a, lane);
@@ -285,12 +288,13 @@ struct WavePlan {
             atomicOr(a.err, kErrLength);
         if (malformed) r.tiles = r.steps = 0;
         S = 1;
-        if (a.split) {
+        chunk = known;
+        if (cut && chunk == 0) {
             // the smallest chunk of C steps at which the units still run in
             // as few rounds as the tiles do (see the host's rule)
             const int items = lane_sum(r.tiles) * a.H_kv;
-            const int target = items <= a.slots / 4 ? a.slots / 2 : (items + a.slots - 1) / a.slots * a.slots;
-            int lo = kMinChunk, hi = 1;
+            const int target = (items + a.slots - 1) / a.slots * a.slots;
+            int lo = kPrefillMinChunk, hi = 1;
             {
                 int mx = r.steps;
 #pragma unroll
@@ -302,8 +306,9 @@ struct WavePlan {
                 if (lane_sum(r.tiles * ((r.steps + mid - 1) / mid)) * a.H_kv <= target) hi = mid;
                 else lo = mid + 1;
             }
-            S = max((r.steps + lo - 1) / lo, 1);
+            chunk = lo;
         }
+        if (cut) S = max((r.steps + chunk - 1) / chunk, 1);
         u_end = lane_scan(r.tiles * S);
         units = __builtin_amdgcn_readlane(u_end, 63);
     }
@@ -420,7 +425,7 @@ __global__ void __launch_bounds__(256) vcopy_kernel(PrefillArgs a) {
     const bool self = a.B <= 64;
     int s_end = 0, total, Lb = 0;
     if (self) {
-        const WavePlan p(a);
+        const WavePlan p(a, false, 0);
         s_end = lane_scan(p.r.steps);
         total = __builtin_amdgcn_readlane(s_end, 63);
         s_end -= p.r.steps;         // first step of this lane's request
@@ -575,8 +580,9 @@ prefill_attn_kernel(PrefillArgs a) {
     const int kq = (int)blockIdx.x / kXcds, xcd = (int)blockIdx.x % kXcds;
     int r, g;
     if (a.B <= 64) {
-        const WavePlan p(a);
+        const WavePlan p(a, a.split, 0);
         units = p.units;
+        if (a.split && blockIdx.x == 0 && tid == 0) *a.chunk = p.chunk;
         const int items = units * a.H_kv, share = (items + kXcds - 1) / kXcds;
         r = xcd * share + kq;
         if (kq >= share || r >= items) return;
@@ -1073,7 +1079,7 @@ template <int D>
 __global__ void __launch_bounds__(256) prefill_merge_kernel(PrefillArgs a) {
     constexpr int NT = D / 32, WPT = 4 * NT;      // waves a tile
     const int lane = threadIdx.x & 63, c = lane & 31, hl = lane >> 5;
-    const WavePlan p(a);
+    const WavePlan p(a, true, __builtin_amdgcn_readfirstlane(*a.chunk));
     const int t_end = lane_scan(p.r.tiles);
     const int tiles = __builtin_amdgcn_readlane(t_end, 63);
     const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
