@@ -294,12 +294,15 @@ struct WavePlan {
             // as few rounds as the tiles do (see the host's rule)
             const int items = lane_sum(r.tiles) * a.H_kv;
             const int target = (items + a.slots - 1) / a.slots * a.slots;
-            int lo = kPrefillMinChunk, hi = 1;
-            {
-                int mx = r.steps;
-#pragma unroll
-                for (int o = 32; o >= 1; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 64));
-                hi = max(__builtin_amdgcn_readfirstlane(mx), lo);
+            // from the even deal of all steps up: rounding up costs a unit more
+            // for each tile at most (long requests: the deal of their whole
+            // 1024 steps, which keeps the sums inside 32 bits)
+            const int long_steps = lane_sum(r.tiles * (r.steps >> 10));
+            const int64_t steps = long_steps > 0 ? (int64_t)long_steps << 10 : lane_sum(r.tiles * r.steps);
+            int lo = max(kPrefillMinChunk, (int)(steps * a.H_kv / max(target, 1))), hi = lo;
+            while (lane_sum(r.tiles * ((r.steps + hi - 1) / hi)) * a.H_kv > target) {
+                lo = hi + 1;
+                hi += (hi >> 2) + 1;
             }
             while (lo < hi) {
                 const int mid = (lo + hi) >> 1;
@@ -669,11 +672,22 @@ prefill_attn_kernel(PrefillArgs a) {
     // LDS, refilled when no copy is in flight, so a step's pages cost LDS
     // reads only; j a multiple of WIN
     auto refill = [&](int j) {
-        const int e1 = min(kPageWindow, PPS * (s_hi - j));   // entries the unit reads
-        for (int e = tid; e < e1; e += 256) pages[e] = bt[min(PPS * j + e, np - 1)];
-        if constexpr (!FP8)
-            for (int e = tid; e < min(WIN, s_hi - j); e += 256)
-                vexps[e] = a.vexp[(int64_t)(vstep0 + j + e) * a.H_kv + g];
+        // the entries the unit reads, all loads out before any is stored
+        const int e0 = max(0, PPS * (s_lo - j)), e1 = min(kPageWindow, PPS * (s_hi - j));
+        int pe[kPageWindow / 256], ve = 0;
+#pragma unroll
+        for (int k = 0; k < kPageWindow / 256; ++k) {
+            const int e = 256 * k + tid;
+            if (e >= e0 && e < e1) pe[k] = bt[min(PPS * j + e, np - 1)];
+        }
+        const bool mine = !FP8 && PPS * tid >= e0 && PPS * tid < e1;
+        if (mine) ve = a.vexp[(int64_t)(vstep0 + j + tid) * a.H_kv + g];
+#pragma unroll
+        for (int k = 0; k < kPageWindow / 256; ++k) {
+            const int e = 256 * k + tid;
+            if (e >= e0 && e < e1) pages[e] = pe[k];
+        }
+        if (mine) vexps[tid] = ve;
         __syncthreads();
     };
     // unit u = 256 k + tid of a step: tensor u / (PPS UPP) (K, V), page
