@@ -150,27 +150,32 @@ int bellman_decode_attention(const bellman_tensor_t *q, const bellman_tensor_t *
                              bellman_tensor_t *out, void *stream);
 
 typedef struct bellman_attn_opts {
-    int32_t max_waves;    /* cap on the waves that share the work; 0 = every wave the
-                             GPU can keep resident.  Fewer waves split fewer
+    int32_t max_waves;    /* cap on the waves that share the work; 0 = one
+                             workgroup of four waves per CU where pages_per_step
+                             and pipeline_depth are 0 too, else every wave the GPU
+                             can keep resident.  Fewer waves split fewer
                              requests (results agree within rounding). */
     int32_t xcd_skew;     /* share weights of the waves of even- and odd-numbered
                              XCDs (workgroup i runs on XCD i mod 8), applied only
                              when every wave gets at least 384 pages (steps x
                              pages per step):
                              0 = the library's choice (on a whole 256-CU device
-                             k = 10 with one workgroup per CU, k = 6 with two;
-                             equal shares otherwise); -1 = equal shares; k in
+                             k = 10 over bf16 pools, k = 6 with two workgroups
+                             per CU; equal shares otherwise); -1 = equal shares; k in
                              1..255 = weights 256 + k : 256 - k.  Results agree
                              within rounding. */
     int32_t pages_per_step; /* 16-token pages per softmax update: 1 or 2 (bf16),
                                1, 2 or 4 (fp8); 0 = the library's choice
                                (4 for fp8 pools; for bf16 pools 1 when
                                B * H_kv * maxP is below 512 pages per wave,
-                               else 2) */
+                               else 2; at head_dim 64 also 2 below 64 pages
+                               where pipeline_depth is 0 too) */
     int32_t pipeline_depth; /* steps of pages in flight per wavefront while it
-                               computes one: 1 (two wavefronts per SIMD) or 2 (one
-                               per SIMD); 0 = the library's choice (2 for bf16,
-                               1 for fp8 pools) */
+                               computes one: 1 (up to two wavefronts per SIMD) or 2
+                               (one per SIMD); 0 = the library's choice (1 for
+                               fp8 pools; for bf16 pools 2, or 1 where
+                               pages_per_step is 0 too and B * H_kv * maxP is
+                               below 512 pages per wave, 64 at head_dim 64) */
     void *event_begin;    /* optional hipEvent_t recorded on the stream right before
                              the main attention kernel (profiling); NULL = none */
     void *event_end;      /* optional hipEvent_t recorded right after it (before the
@@ -183,7 +188,7 @@ typedef struct bellman_attn_opts {
                              SIMD.  A timing record: the results are those of the
                              untraced call.  Built for head_dim 128 at the default
                              steps (bf16: pages_per_step 1 or 2 with
-                             pipeline_depth 2; fp8: 4 pages, depth 1); other
+                             pipeline_depth 0 or 2; fp8: 4 pages, depth 1); other
                              shapes return BELLMAN_ERR_UNSUPPORTED.  NULL = none */
 } bellman_attn_opts_t;
 
@@ -211,8 +216,8 @@ int bellman_decode_attention_opts(const bellman_tensor_t *q, const bellman_tenso
  * ends, instead of the growable workspace.  A call needs
  *     256 + 16 W + 8 S + 4 D S   bytes (regions rounded up to 256 B),
  *     S = 2 W G partial slots,
- * W the waves it uses (1024 for bf16 and 2048 for fp8 pools on a whole
- * MI355X, or max_waves if smaller): up to G = 16 at D = 128 for bf16 pools
+ * W the waves the GPU can hold (1024 for bf16 and 2048 for fp8 pools on a
+ * whole MI355X, or max_waves if smaller): up to G = 16 at D = 128 for bf16 pools
  * and G = 8 for fp8 pools by default; fp8 pools with G = 16 need
  * max_waves <= 1900.  A call that needs more is rejected with
  * BELLMAN_ERR_UNSUPPORTED before anything is enqueued.  Every call on one

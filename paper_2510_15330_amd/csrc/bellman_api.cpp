@@ -33,10 +33,12 @@ int fail(int code, const char* fmt, ...) {
 
 // ------------------------------------------------------------- workspace ---
 
-constexpr int kXcdSkew = 10;          // share weights 266 : 246, even : odd XCDs (measured best of 0-28)
-constexpr int kXcdSkew2 = 6;          // the same with two workgroups per CU (fp8 stress batch: best of 0, 6, 12, 20)
+constexpr int kXcdSkew = 10;          // share weights 266 : 246, even : odd XCDs (bf16; measured best of 0-28)
+constexpr int kXcdSkew2 = 6;          // the same with two workgroups per CU (fp8 stress batch: best of 0, 6, 12, 20);
+                                      // fp8 with one: equal shares (400 requests of 3-5k tokens 510 us, 516-519 at 6-14)
 constexpr int kMaxAttnBatch = 8192;  // lengths every attention wave reads to find its share
-constexpr double kShortSharePages = 512;   // below this many table pages a wave: one page per step
+constexpr double kShortSharePages = 512;   // below this many table pages a wave: short shares (see their use)
+constexpr double kShortSharePages64 = 64;  // the same for depth 1 at head_dim 64
 
 // The growable per-device workspace.  Growing it allocates a larger block
 // and keeps the old one alive until bellman_shutdown, so kernels already
@@ -298,30 +300,45 @@ int decode_attention(const bellman_tensor_t* q, const bellman_tensor_t* k_pages,
             return fail(BELLMAN_ERR_INVALID_ARG, "xcd_skew %d not in [-1, %d]", skew_opt, kMaxSkew);
     }
     if (pps == 4 && !ps.fp8) return fail(BELLMAN_ERR_UNSUPPORTED, "pages_per_step 4 is built for fp8 pools only");
-    if (depth == 0) depth = ps.fp8 ? 1 : 2;  // measured: fp8 steps compute more per byte
+    const bool chosen = pps == 0 && depth == 0;   // the step is the library's choice
+    if (depth == 0) depth = ps.fp8 ? 1 : 2;
     if (B == 0) return BELLMAN_OK;
 
     int dev;
     if ((rc = current_device(&dev))) return rc;
     if ((rc = cu_count(dev))) return rc;
+    // Pages the block table has room for, a wave of one workgroup per CU: what
+    // is known here of the shares' length, without a device read.
+    int64_t w_est = (int64_t)g_cu_count[dev] * (kAttnBlock / kWaveSize) * (depth == 2 || chosen ? 1 : 2);
+    if (max_waves > 0 && w_est > max_waves) w_est = max_waves;
+    const double table_pages_per_wave = (double)B * ps.H_kv * (double)max_pages / (double)w_est;
     if (pps == 0) {
         // bf16: two pages per step, or one when the block table leaves room
         // for few pages per wave (short shares: the finer step shortens the
-        // ramp and the tail; measured 121 against 126 us on 64 requests of
-        // 1-4k tokens, while 256 requests of 6-13.5k tokens run faster with
-        // two).  Decided from the table's width, so no device read is needed.
-        int64_t w_est = (int64_t)g_cu_count[dev] * (kAttnBlock / kWaveSize) * (depth == 2 ? 1 : 2);
-        if (max_waves > 0 && w_est > max_waves) w_est = max_waves;
-        const double table_pages_per_wave = (double)B * ps.H_kv * (double)max_pages / (double)w_est;
+        // ramp and the tail; 121 against 126 us on 64 requests of 1-4k tokens,
+        // while 256 requests of 6-13.5k tokens run faster with two).
         pps = ps.fp8 ? 4 : (table_pages_per_wave < kShortSharePages ? 1 : 2);
     }
-    if (step && !attention_step_built(pps, depth, ps.fp8))
+    // Short bf16 shares run one step ahead instead of two, still one wave a
+    // SIMD: the pipeline fills and drains a step sooner (calls, depth 2 / 1:
+    // one request of 2,000 tokens 14.4 / 13.1 us, 64 of 50-200 17.0 / 15.3, 64
+    // of 1-4k 110.6 / 108.3, 64 of 6-10k 332.8 / 331.8; from 512 table pages a
+    // wave depth 2 wins, 654 against 671 us on 128 of 6-10k).  At head_dim 64
+    // two pages make a step of the same bytes, and it pays for the shortest
+    // shares only (64 of 50-200 13.0 / 12.9 us, 16 of 1-2k 17.6 / 16.2, 64 of
+    // 1-4k 59.4 / 60.3).
+    const int asked_depth = depth;
+    if (chosen && !ps.fp8 && table_pages_per_wave < (ps.D == 128 ? kShortSharePages : kShortSharePages64)) {
+        if (ps.D == 64) pps = 2;
+        if (!step) depth = 1;               // (the step is built at depth 2)
+    }
+    if (step && !attention_step_built(pps, asked_depth, ps.fp8))
         return fail(BELLMAN_ERR_UNSUPPORTED,
                     "decode step: built for the default steps only (bf16: 1 or 2 pages, depth 2; fp8: 4 pages, "
                     "depth 1)");
     int64_t* wave_times = opts ? opts->wave_times : nullptr;
     if (step && wave_times) return fail(BELLMAN_ERR_UNSUPPORTED, "decode step: wave_times is not built for it");
-    if (wave_times && !attention_traced(pps, depth, ps.fp8, ps.D))
+    if (wave_times && !attention_traced(pps, asked_depth, ps.fp8, ps.D))
         return fail(BELLMAN_ERR_UNSUPPORTED,
                     "wave_times: traced kernels are built for head_dim 128 at the default steps only");
     if (wave_times && !aligned(wave_times, 8)) return fail(BELLMAN_ERR_UNSUPPORTED, "wave_times must be 8-byte aligned");
@@ -330,17 +347,29 @@ int decode_attention(const bellman_tensor_t* q, const bellman_tensor_t* k_pages,
         bpc = attention_blocks_per_cu(pps, depth, ps.fp8, ps.D);
         if (depth == 2) bpc = 1;  // one wavefront per SIMD
     }
-    // Every resident wave takes an equal share of the flattened step stream.
-    int64_t waves = (int64_t)g_cu_count[dev] * bpc * (kAttnBlock / kWaveSize);
+    // Every resident wave takes an equal share of the flattened step stream;
+    // the library's own steps run one workgroup a CU.  Over fp8 pools two fit,
+    // but the second one's waves cost more (twice the plans, ramps, segment
+    // ends and partial pieces, and a memory system that streams fewer waves
+    // faster) than they hide.  Calls, two workgroups / one with equal shares:
+    // 32 requests of 0.5-8k tokens 56.8 / 50.6 us, 64 of 1-4k 67.4 / 64.3, 64
+    // of 1-4k at head_dim 64 48.3 / 41.3, 400 of 3-5k 541 / 510, 512 with Zipf
+    // lengths to 16k 437 / 431.
+    const int wgs = chosen ? 1 : bpc;
+    const int64_t cu_waves = (int64_t)g_cu_count[dev] * (kAttnBlock / kWaveSize);
+    int64_t waves = cu_waves * wgs, sized = cu_waves * (depth == asked_depth ? bpc : 1);
     if (max_waves > 0 && waves > max_waves) waves = max_waves;
+    if (max_waves > 0 && sized > max_waves) sized = max_waves;
     const int64_t grid = (waves + (kAttnBlock / kWaveSize) - 1) / (kAttnBlock / kWaveSize);
 
     if (waves > kMaxWaves) return fail(BELLMAN_ERR_UNSUPPORTED, "%lld waves > %d", (long long)waves, kMaxWaves);
     // two partial slots per wave and query head: a wave's range cuts at most
     // the request it starts in and the one it ends in
     const size_t off_cuts = kWsHeader;
-    const size_t off_ml = off_cuts + align256(sizeof(int4) * (size_t)waves);
-    const size_t slots = 2 * (size_t)waves * (size_t)G;
+    // (sized for every wave the device could hold, so that the limits of the
+    // fixed array do not depend on the choice above)
+    const size_t off_ml = off_cuts + align256(sizeof(int4) * (size_t)sized);
+    const size_t slots = 2 * (size_t)sized * (size_t)G;
     const size_t off_o = off_ml + align256(sizeof(float2) * slots);
     const size_t total = off_o + align256(sizeof(float) * slots * (size_t)ps.D);
     hipStream_t s = (hipStream_t)stream;
@@ -385,7 +414,7 @@ int decode_attention(const bellman_tensor_t* q, const bellman_tensor_t* k_pages,
     // The default XCD weights were measured on a whole MI355X (256 CUs,
     // workgroup i on XCD i mod 8), with one and with two workgroups per CU;
     // partitioned devices keep equal shares.
-    if (skew_opt == 0) a.skew = g_cu_count[dev] == 256 ? (bpc == 1 ? kXcdSkew : kXcdSkew2) : 0;
+    if (skew_opt == 0) a.skew = g_cu_count[dev] != 256 ? 0 : wgs == 2 ? kXcdSkew2 : ps.fp8 ? 0 : kXcdSkew;
     else a.skew = skew_opt < 0 ? 0 : skew_opt;
     a.err = err;
     a.cuts = (int4*)(base + off_cuts);

@@ -1226,8 +1226,8 @@ attn_mfma_kernel(AttnArgs a) {
         if constexpr (DEPTH >= 3) step(std::integral_constant<int, 3>{});
         if (!cur[0].live) break;
         if constexpr (DEPTH == 1) {
-            // Two workgroups share each CU at this depth (one wave of each per
-            // SIMD), and the wave arbiter favours the older: it finished well
+            // Two workgroups can share each CU at this depth (one wave of each
+            // per SIMD), and the wave arbiter favours the older: it finished well
             // ahead and left the other alone on its CU (per-wave timing
             // records, 512-request fp8 batch).  A wave with more of its range
             // left now issues first.
@@ -1467,9 +1467,10 @@ void launch_kv_append(const AppendArgs& a, hipStream_t s) {
 }
 
 // The shapes built with a traced twin: head_dim 128 at the library's default
-// steps (bf16: one or two pages, depth 2; fp8: four pages, depth 1).
+// steps (bf16: one or two pages, depth 2, or one page, depth 1; fp8: four
+// pages, depth 1).
 template <int D, bool FP8, int PP, int DEPTH>
-constexpr bool kTraced = D == 128 && (FP8 ? (PP == 4 && DEPTH == 1) : (PP <= 2 && DEPTH == 2));
+constexpr bool kTraced = D == 128 && (FP8 ? (PP == 4 && DEPTH == 1) : (PP <= 2 && DEPTH == 2) || (PP == 1 && DEPTH == 1));
 
 // The shapes built with a decode-step twin (the append fused in): the
 // library's default steps, both head sizes.
