@@ -246,10 +246,10 @@ __global__ void lens_kernel(WriteArgs a) {
 //
 // Measured, whole prompt steps, against rows of one query head each, no key
 // split and the planning launch: one 2048-token chunk after 4,900 tokens on
-// 4/2 heads (64 tiles: 512 units of 14 steps) 171 -> 59 us, the attention
-// alone 141 -> 41 us and 8 us of merge (256 units: 50 + 6 us); eight chats' 16-256 new tokens after
-// 2-8k (336 tiles instead of 416, 488 units) 207 -> 172 us; four prompts of
-// 6-12k (7584 tiles, never cut) the same.
+// 4/2 heads (64 tiles: 512 units of 14 steps) 171 -> 56 us, the attention
+// alone 141 -> 41 us and 8 us of merge (256 units: 50 + 6 us); eight chats'
+// 16-256 new tokens after 2-8k (336 tiles instead of 416, 488 units) 205 ->
+// 163 us; four prompts of 6-12k (7584 tiles, never cut) 2017 -> 2006 us.
 struct ReqPlan {
     int q0, n, L, tiles, steps;   // steps: 64-key steps of its keys; 0 with no tiles
     bool bad;
@@ -665,7 +665,9 @@ prefill_attn_kernel(PrefillArgs a) {
     f32x16 o[D / 32];
 #pragma unroll
     for (int t = 0; t < D / 32; ++t) o[t] = f32x16{};
-    float m = -INFINITY, l = 0.f;
+    // m starts at the lowest finite value: scores of -inf alone weigh nothing
+    // (l = 0), and only a NaN makes l one
+    float m = -__FLT_MAX__, l = 0.f;
     bool bad = false;
 
     // the block-table entries (and value scales) of WIN steps at a time sit in
@@ -1056,9 +1058,10 @@ prefill_attn_kernel(PrefillArgs a) {
     const float f = v_scale / l_tot;
     if (S > 1) {
         // a piece: its rows' (m, l) and normalised O, in the lanes' own order
-        // (dead, m = -inf, where the row sees no key of this unit)
+        // (dead, m = -inf, where the row sees no key of this unit or scores of
+        // -inf alone; a NaN sum stays and poisons the row)
         const int64_t piece = (int64_t)r * 4 + w;
-        const bool dead = s_lo >= s_hi || pos < KS * s_lo;
+        const bool dead = s_lo >= s_hi || pos < KS * s_lo || l_tot == 0.f;
         if (hl == 0) a.part_ml[piece * 32 + c] = make_float2(dead ? -INFINITY : m, l_tot);
         f32x4* po = (f32x4*)a.part_o + piece * (D / 8) * 64 + lane;
 #pragma unroll

@@ -272,6 +272,29 @@ def test_prefill_key_split(case, kv):
     assert_close(_out_f64(out), _oracle_prefill(w, kp, vp), "bf16", f"{name} {kv}")
 
 
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+def test_prefill_key_split_nan_and_inf_shares(kv):
+    # keys 1024..3071 of 5,000, whole shares of a cut tile: NaN in KV head 0
+    # (every row of its query heads is NaN), and over bf16 pools scores of
+    # -inf in KV head 1 (weight 0, as the oracle has it)
+    w = wl.build_prefill(cached=[5000], new=[3], H_q=4, H_kv=2, D=128, seed=9, device="cuda", kv=kv)
+    w.q[:, 2:, 0] = 1.0
+    _write(w)
+    pages = w.block_table[0, 64:192].long()
+    if kv == "fp8":
+        w.k_pages[pages, 0] = 0x7F
+    else:
+        w.k_pages[pages, 0] = float("nan")
+        w.k_pages[pages, 1, 0, :, 0] = -float("inf")
+    out = torch.zeros((w.T, 4, 128), dtype=torch.bfloat16, device="cuda")
+    _attend(w, w.q, out)
+    bl.device_errors()
+    got = _out_f64(out)
+    assert np.isnan(got[:, :2]).all()
+    kp, vp = _host_pools(w)
+    assert_close(got[:, 2:], _oracle_prefill(w, kp, vp)[:, 2:], "bf16", f"-inf share {kv}")
+
+
 def _sweep_counts(rng, B, edge):
     out = []
     for _ in range(B):
