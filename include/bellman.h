@@ -305,22 +305,26 @@ int bellman_kv_write(const bellman_tensor_t *k_new, const bellman_tensor_t *v_ne
  *                a malformed request (n_b > L_b, rows past T, L_b past the
  *                table: flag 2) are not written; a q_start that decreases, starts below
  *                0 or ends past T writes no row at all (flag 2).
- * Each workgroup takes 128 query rows of one request and one query head;
- * QK^T runs on the bf16 matrix cores and PV on the fp16 ones, in one pass
- * with P rounded to fp16 (11 significant bits; P rounded to bf16 once would
- * spend the bf16 error budget).  Over bf16 pools the values the call reads
- * are first copied into the workspace as fp16, each (request, KV head) at
+ * Each workgroup takes 128 (token, query head) rows of one request and KV
+ * head over all of their keys, or over a share of them where the rows would
+ * leave the device idle (merged in fp32 by a second pass).  QK^T runs on the
+ * bf16 matrix cores and PV on the fp16 ones, in one pass with P rounded to
+ * fp16 (11 significant bits; P rounded to bf16 once would spend the bf16
+ * error budget).  Over bf16 pools the values the call reads are first copied
+ * into the workspace as fp16, each 64-token step of a (request, KV head) at
  * the power of two 2^e that brings its largest magnitude M into
  * [2^14, 2^15): every value of at least M 2^-28 converts exactly, none
- * overflows, and the output is scaled back by 2^-e.  Over fp8 pools the
+ * overflows, and the weights and the output carry 2^-e.  Over fp8 pools the
  * codes are staged in LDS as bytes and widened exactly at the operand load
  * (K to bf16, V to fp16); the K scale folds into the softmax scale and the
  * V scale into the final normalisation.  Scratch in the per-device
- * workspace: 2 (B + 1) + B H_kv integers, and over bf16 pools B maxP
- * (4 + 4 H_kv + 32 D H_kv) bytes more for the value copy and its
- * bookkeeping (maxP = the block table's width).  Like bellman_kv_write, once
- * the workspace has grown to the call's size the call enqueues only kernels
- * (graph-capturable). */
+ * workspace: 3 KiB + 4 (B + 1) bytes; over bf16 pools, for the value copy
+ * and its bookkeeping, B ceil(maxP / 4) (4 + 4 H_kv + 128 D H_kv) +
+ * 4 (B + 1) bytes more (maxP = the block table's width); and where keys are
+ * shared out 128 (4 D + 8) bytes a share, at most four shares a CU (a capture
+ * with no room for those runs uncut; results agree within rounding).  Like
+ * bellman_kv_write, once the workspace has grown to the call's size the call
+ * enqueues only kernels (graph-capturable). */
 int bellman_prefill_attention(const bellman_tensor_t *q, const bellman_tensor_t *k_pages,
                               const bellman_tensor_t *v_pages, const bellman_tensor_t *block_table,
                               const bellman_tensor_t *seq_lens, const bellman_tensor_t *q_start,

@@ -87,7 +87,9 @@ int ensure_workspace(int dev, size_t bytes, hipStream_t stream, char** base) {
             return fail(BELLMAN_ERR_UNSUPPORTED,
                         "the workspace would have to grow to %zu bytes during graph capture; make the same call, "
                         "or bellman_reserve_workspace, before capturing", bytes);
-        size_t want = bytes + bytes / 4;
+        // room to grow: small blocks fourfold, so that the tile padding of
+        // narrow tables' value copies fits what other shapes have reserved
+        size_t want = bytes + std::max(bytes / 4, std::min(3 * bytes, (size_t)256 << 20));
         want = (want + 0xFFFFF) & ~(size_t)0xFFFFF;
         void* p = nullptr;
         e = hipMalloc(&p, want);
@@ -101,6 +103,13 @@ int ensure_workspace(int dev, size_t bytes, hipStream_t stream, char** base) {
     }
     *base = w.base;
     return BELLMAN_OK;
+}
+
+// Whether the stream is being captured and the workspace has no room for `bytes`.
+bool capture_short_of(int dev, size_t bytes, hipStream_t stream) {
+    std::lock_guard<std::mutex> lock(g_ws_mutex);
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return g_ws[dev].cap < bytes && hipStreamIsCapturing(stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -744,18 +753,26 @@ int bellman_prefill_attention_opts(const bellman_tensor_t* q, const bellman_tens
 
     const bool planned = B > 64;           // by a kernel of its own (each wave plans for itself up to 64)
     const size_t max_steps = (size_t)B * (size_t)((max_pages + 3) / 4);
-    const size_t piece_rows = a.split ? (size_t)a.max_units * kPrefillRows : 0;
     const size_t off_tiles = kWsHeader;
     const size_t off_chunk = off_tiles + align256(planned ? (size_t)(B + 1) * 4 : 0);
-    const size_t off_ml = off_chunk + 256;
-    const size_t off_o = off_ml + align256(piece_rows * sizeof(float2));
-    const size_t off_steps = off_o + align256(piece_rows * ps.D * sizeof(float));
+    const size_t off_steps = off_chunk + 256;
     const size_t off_req = off_steps + align256(planned && !ps.fp8 ? (size_t)(B + 1) * 4 : 0);
     const size_t off_exp = off_req + align256(planned && !ps.fp8 ? max_steps * 4 : 0);
     const size_t off_copy = off_exp + align256(ps.fp8 ? 0 : max_steps * ps.H_kv * 4);
-    const size_t total = off_copy + align256(ps.fp8 ? 0 : max_steps * ps.H_kv * 4 * page_head_bytes);
+    const size_t off_ml = off_copy + align256(ps.fp8 ? 0 : max_steps * ps.H_kv * 4 * page_head_bytes);
+    const size_t piece_rows = a.split ? (size_t)a.max_units * kPrefillRows : 0;
+    const size_t off_o = off_ml + align256(piece_rows * sizeof(float2));
+    size_t total = off_o + align256(piece_rows * ps.D * sizeof(float));
 
     hipStream_t s = (hipStream_t)stream;
+    // The pieces grow with the call's tokens, the rest only with the batch
+    // and the table: a capture of more tokens than the calls before it had
+    // runs uncut where the pieces would not fit.
+    if (a.split && capture_short_of(dev, total, s)) {
+        a.split = 0;
+        a.max_units = a.max_tiles;
+        total = off_ml;
+    }
     char* base;
     if ((rc = ensure_workspace(dev, total, s, &base))) return rc;
     int32_t* err;

@@ -169,3 +169,40 @@ def test_graph_survives_workspace_growth():
     assert ei.value.code == -2 and "graph capture" in str(ei.value)
     del g2
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+def test_prompt_capture_of_more_tokens_than_before(kv):
+    """The key-split's pieces grow with a call's tokens: a capture whose
+    workspace was grown by a call of fewer runs uncut, and agrees with the cut
+    call (both carry their output's rounding to bf16, 2^-9 each)."""
+    bl.shutdown()
+    w = wl.build_prefill(cached=[2000], new=[600], H_q=4, H_kv=2, D=128, seed=3, device="cuda", kv=kv)
+    bl.kv_write(w.k_new, w.v_new, w.k_pages, w.v_pages, w.block_table, w.seq_lens, w.q_start)
+    out = torch.empty((w.T, 4, 128), dtype=torch.bfloat16, device="cuda")
+    # reserved: what the call takes beside the pieces
+    steps, codes = -(-w.block_table.shape[1] // 4), kv == "fp8"
+    bl.reserve_workspace(3072 + (0 if codes else steps * (4 + 4 * 2 + 128 * 128 * 2)))
+
+    def attend():
+        bl.prefill_attention(w.q, w.k_pages, w.v_pages, w.block_table, w.seq_lens, w.q_start, w.scale, out,
+                             k_scale=w.k_scale, v_scale=w.v_scale)
+
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        attend()
+    got = []
+    for _ in range(3):
+        out.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        got.append(out.clone())
+    out.fill_(float("nan"))
+    attend()                                       # eager: grows the workspace and cuts the keys
+    torch.cuda.synchronize()
+    for i, o in enumerate(got):
+        assert torch.isfinite(o).all() and torch.equal(_bits(o), _bits(got[0])), f"replay {i}"
+        rel = ((o.double() - out.double()).norm() / out.double().norm()).item()
+        assert rel <= 2 * 2.0 ** -9, (i, rel)
+    del g
+    torch.cuda.synchronize()
