@@ -1,10 +1,10 @@
 // The decode-attention work split: which contiguous range of the flattened
 // step stream each wave takes, and its inverse (which wave took a given
-// step).  The attention kernel finds its own range with share_bound; the
-// merge kernel finds the waves that covered a cut (request, KV head) with
-// wave_of.  The two must agree exactly, so both are written once here and
-// compiled for the host as well, where a test checks that wave_of inverts
-// share_bound.
+// step).  A wave of the attention kernel finds its own range with
+// share_bound, and the last wave that covers the (request, KV head) its range
+// cuts with wave_of; the merge reads that from its record.  The two must agree
+// exactly, so both are written once here and compiled for the host as well,
+// where a test checks that wave_of inverts share_bound.
 //
 // The work of a call is the flattened sequence of P units (request b, KV
 // head g, step j), request-major, then head, then step, where step j of a
