@@ -314,7 +314,9 @@ int bellman_kv_write(const bellman_tensor_t *k_new, const bellman_tensor_t *v_ne
  * into the workspace as fp16, each 64-token step of a (request, KV head) at
  * the power of two 2^e that brings its largest magnitude M into
  * [2^14, 2^15): every value of at least M 2^-28 converts exactly, none
- * overflows, and the weights and the output carry 2^-e.  Over fp8 pools the
+ * overflows; the output is kept at the finest step's scale, a coarser step's
+ * weights are multiplied by the difference, and 2^-e is taken out at the end
+ * (values more than 2^63 below the largest of a key range lose bits).  Over fp8 pools the
  * codes are staged in LDS as bytes and widened exactly at the operand load
  * (K to bf16, V to fp16); the K scale folds into the softmax scale and the
  * V scale into the final normalisation.  Scratch in the per-device

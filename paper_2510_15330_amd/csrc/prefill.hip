@@ -400,7 +400,8 @@ __global__ void __launch_bounds__(kPlanThreads) prefill_plan_kernel(PrefillArgs 
 // slots past its length zero.  A scale a step needs one pass over the values
 // (a scale a (request, head) took three: the maximum of every tile, of every
 // (request, head), then the copy; 33 against 18 us on 36k tokens of 8 heads);
-// the attention works the difference of two steps' scales into the weights.
+// the attention holds its output at the finest step's scale and works what a
+// coarser step's is below that into its weights.
 constexpr int kAnyExp = 1 << 20;   // the step's values are all zero: any scale holds
 
 // the scale exponent e for a largest magnitude whose float bits are mb
@@ -516,15 +517,25 @@ __global__ void __launch_bounds__(256) vcopy_kernel(PrefillArgs a) {
 // 16-byte run of each dim-major V row.  Online softmax in base 2 with a lazy
 // max: O and l are rescaled only when some column's max grows by more than
 // 2^8, so P stays below 2^8.  P enters as fp16, rounded once (2^-12 of each
-// weight, against the output's own 2^-9).
+// weight above 2^-14, against the output's own 2^-9).
 //
 // The loop is software-pipelined: step s masks and takes the max of S(s)
 // (computed one step earlier), then issues the MFMAs of S(s + 1)
 // interleaved with the exponentials of P(s), then the PV MFMAs of step s.
 constexpr float kLazyMax = 8.0f;
-// bf16 pools: a step's scale may be 2^7 coarser than the reference (P, below
-// 2^8, times 2^7 stays inside fp16) or 2^20 finer
-constexpr int kMaxCoarser = 7, kMaxFiner = 20;
+// bf16 pools: O is held at a scale 2^eref, never coarser than the step at
+// hand, so that no weight is made smaller before it is rounded to fp16 (whose
+// numbers below 2^-14 lose a bit a factor of two): O moves up to a finer
+// step's scale, and a coarser step's weights are multiplied by up to 2^7 (P,
+// below 2^8, stays inside fp16) before O moves down to it.  Holding O at the
+// first step's scale and multiplying finer steps' weights by 2^-d instead
+// left them 11 - (d - 14) bits: rows made of values 2^20 finer than a large
+// step of small weight came out 0.1 to 0.3 off, and now 2e-3 (their bf16
+// rounding); four prompts of 6-12k tokens 2017 and 2021 us, runs 1.3% apart.
+// O stays within 2^64 of the coarsest step seen (2^64 2^15 values at weights
+// of 2^8 from 2^24 keys stay inside fp32); values finer still, below M 2^-63,
+// take smaller weights.
+constexpr int kMaxCoarser = 7, kMaxRise = 64;
 constexpr int kPageWindow = 1024;   // block-table entries staged in LDS
 constexpr int kXcds = 8;            // accelerator complexes; workgroup i runs on XCD i % 8
 // VALU instructions of the softmax placed between consecutive S MFMAs
@@ -766,14 +777,6 @@ prefill_attn_kernel(PrefillArgs a) {
                                              0, 0);
         }
     };
-    // a step whose values' scale is 2^d finer than the reference: its weights
-    // enter PV as 2^-d P (d <= kMaxFiner, where they are still normal numbers
-    // in the row sum; values finer than that give up the excess in LDS, at an
-    // absolute error far below the reference's)
-    auto coarsen = [&](uint16_t* V, int by) {
-        const _Float16 f = (_Float16)(by > 24 ? 0.f : pow2f(-by));
-        for (int e = tid; e < KT; e += 256) ((_Float16*)V)[e] *= f;
-    };
     // fp8: V slots of keys >= L hold no token (NaN in a pool); P is 0 there,
     // and 0 * NaN must not reach O, so the tail step's slots are cleared (the
     // fp16 copy holds zeros there)
@@ -856,16 +859,14 @@ prefill_attn_kernel(PrefillArgs a) {
         }
     };
 
-    // bf16 pools: O is held at the scale 2^eref (kAnyExp while every value was
-    // zero), the same in all waves; a step whose values are at 2^(eref + d)
-    // takes its weights times 2^-d.  e1, e2: the scales of steps s, s + 1
-    // (before step s + 2's is read)
-    int eref = kAnyExp, e1 = kAnyExp, e2 = kAnyExp;
+    // bf16 pools: the scale exponent of O (kAnyExp while every value was
+    // zero), the same in all waves, and the lowest of the steps so far.  e1,
+    // e2: the scales of steps s, s + 1 (before step s + 2's is read)
+    int eref = kAnyExp, elow = kAnyExp, e1 = kAnyExp, e2 = kAnyExp;
     auto vexp_of = [&](int j) {
         if constexpr (FP8) return 0;
         else return __builtin_amdgcn_readfirstlane(vexps[j % WIN]);
     };
-    auto finer = [&](int e) { return e == kAnyExp || eref == kAnyExp ? 0 : e - eref; };
 
     // prologue: K and V of the first step, K of the next, S of the first
     if (s_lo < s_hi) {
@@ -916,20 +917,24 @@ prefill_attn_kernel(PrefillArgs a) {
             dma(kbase, off2, k_wr, false);
         }
         // the weights' factor 2^-d of this step, as the exponent's offset, and
-        // 2^d, which takes their sum back
+        // 2^d, which takes their sum back (d in [-7, 0], above 0 only past
+        // kMaxRise)
         float d = 0.f, pd = 1.f;
         if constexpr (!FP8) {
-            if (eref == kAnyExp) eref = e1;        // O is zero so far
-            int di = min(finer(e1), kMaxFiner);
-            if (di < -kMaxCoarser) {               // values far larger than any before: O moves to their scale
-                const float f = di < -126 ? 0.f : pow2f(di);
+            if (e1 != kAnyExp) {
+                elow = min(elow, e1);
+                if (eref == kAnyExp) eref = e1;    // O is zero so far
+                const int to = min(e1, elow + kMaxRise);
+                if (to > eref || to < eref - kMaxCoarser) {
+                    const float f = to - eref < -126 ? 0.f : pow2f(to - eref);
 #pragma unroll
-                for (int t = 0; t < D / 32; ++t) o[t] *= f;
-                eref = e1;
-                di = 0;
+                    for (int t = 0; t < D / 32; ++t) o[t] *= f;
+                    eref = to;
+                }
+                const int di = min(e1 - eref, kMaxRise);
+                d = (float)di;
+                pd = pow2f(di);
             }
-            d = (float)di;
-            pd = pow2f(di);
         }
         uint32_t ph[NH][8];   // P as fp16 pairs
         if (s < wave_steps) {
@@ -1035,10 +1040,6 @@ prefill_attn_kernel(PrefillArgs a) {
                 clear_tail(s + 1, v_wr);
                 __syncthreads();
             }
-            if (!FP8 && finer(e2) > kMaxFiner) {
-                coarsen(v_wr, finer(e2) - kMaxFiner);
-                __syncthreads();
-            }
         }
 #pragma unroll
         for (int q = 0; q < PPS; ++q) off1[q] = off2[q];
@@ -1053,9 +1054,10 @@ prefill_attn_kernel(PrefillArgs a) {
     if (bad && lane == 0) atomicOr(a.err, kErrPage);
     if (rw >= rows) return;
     const float l_tot = l + swap_halves(l);
-    // fp8: the V scale; bf16: undo the values' scale
-    if constexpr (!FP8) v_scale = eref == kAnyExp ? 1.f : pow2f(-eref);
-    const float f = v_scale / l_tot;
+    // fp8: the V scale; bf16: undo the values' scale, in a multiplication of
+    // its own (2^-eref / l may be subnormal where the output is not)
+    const float f = (FP8 ? v_scale : 1.f) / l_tot, unscale = FP8 || eref == kAnyExp ? 1.f : pow2f(-eref);
+    auto out_of = [&](float x) { return FP8 ? x * f : x * f * unscale; };
     if (S > 1) {
         // a piece: its rows' (m, l) and normalised O, in the lanes' own order
         // (dead, m = -inf, where the row sees no key of this unit or scores of
@@ -1068,8 +1070,8 @@ prefill_attn_kernel(PrefillArgs a) {
         for (int t = 0; t < D / 32; ++t)
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4)
-                po[(4 * t + r4) * 64] = f32x4{o[t][4 * r4] * f, o[t][4 * r4 + 1] * f, o[t][4 * r4 + 2] * f,
-                                              o[t][4 * r4 + 3] * f};
+                po[(4 * t + r4) * 64] = f32x4{out_of(o[t][4 * r4]), out_of(o[t][4 * r4 + 1]), out_of(o[t][4 * r4 + 2]),
+                                              out_of(o[t][4 * r4 + 3])};
         return;
     }
     if (rw + c < rows) {
@@ -1078,8 +1080,8 @@ prefill_attn_kernel(PrefillArgs a) {
         for (int t = 0; t < D / 32; ++t)
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
-                const f32x2 v01 = {o[t][4 * r4] * f, o[t][4 * r4 + 1] * f};
-                const f32x2 v23 = {o[t][4 * r4 + 2] * f, o[t][4 * r4 + 3] * f};
+                const f32x2 v01 = {out_of(o[t][4 * r4]), out_of(o[t][4 * r4 + 1])};
+                const f32x2 v23 = {out_of(o[t][4 * r4 + 2]), out_of(o[t][4 * r4 + 3])};
                 u32x2 pk;
                 pk.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(v01, bf16x2));
                 pk.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(v23, bf16x2));

@@ -248,6 +248,40 @@ def test_prefill_value_magnitudes_by_step():
     assert np.all(np.isfinite(got)) and rel.max() <= 2.5e-3, rel.max()
 
 
+# (steps that are 2^d larger, d) of each request, over 64-key steps
+FAR_STEPS = [([0], 6), ([0], 12), ([0], 14), ([0], 16), ([0], 20), ([0], 22), ([0], 30), ([0], 56),
+             ([3], 24), ([0, 4, 5, 9], 21), ([1, 3, 5, 7, 9, 11], 18), ([0, 2, 4, 6, 8, 10], 33)]
+
+
+@pytest.mark.parametrize("cached,split", [(380, False), (2000, True)])   # a table of 512 tokens is never cut
+@pytest.mark.parametrize("H_q,H_kv,D", [(4, 2, 128), (3, 1, 64)])
+def test_prefill_large_values_of_small_weight(cached, split, H_q, H_kv, D):
+    # steps whose values are 2^d larger than the others' but weigh 2^-(d + 20)
+    # in every row: the output is made of the ordinary values, whose weights
+    # must keep their bits whatever the large steps' scale was.  The bound is
+    # that of test_prefill_value_magnitudes_by_step
+    B, n = len(FAR_STEPS), 100
+    w = wl.build_prefill(cached=[cached] * B, new=[n] * B, H_q=H_q, H_kv=H_kv, D=D, seed=D + cached, device="cuda",
+                         extra_table=0)
+    _write(w)
+    assert (w.block_table.shape[1] * 16 > 512) == split
+    w.q[:, :, 0] = 8.0
+    unit = 8.0 * w.scale * np.log2(np.e)                    # log2 weight of a key whose dim 0 grows by one
+    for b, (steps, d) in enumerate(FAR_STEPS):
+        for s in steps:
+            pages = w.block_table[b, 4 * s:min(4 * s + 4, cached // 16)].long()
+            w.v_pages[pages] = (w.v_pages[pages].double() * 2.0 ** d).to(torch.bfloat16)
+            w.k_pages[pages, :, 0, :, 0] = -(d + 20 + 8) / unit      # (8: the spread of the other dims)
+    out = torch.full((w.T, H_q, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    _attend(w, w.q, out)
+    assert bl.device_errors() == 0
+    kp, vp = _host_pools(w)
+    ref, got = _oracle_prefill(w, kp, vp), _out_f64(out)
+    rel = np.linalg.norm(got - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
+    worst = [(FAR_STEPS[b], float(rel[n * b:n * (b + 1)].max())) for b in range(B)]
+    assert np.all(np.isfinite(got)) and rel.max() <= 2.5e-3, worst
+
+
 SPLIT_CASES = [
     # name, cached, new, H_q, H_kv, D: few tiles, so that their keys are cut
     ("one_token", [5000], [1], 4, 1, 128),
