@@ -1091,11 +1091,14 @@ attn_mfma_kernel(AttnArgs a) {
         }
     };
 
+    // m starts at the lowest finite value: scores of -inf alone weigh nothing
+    // (l = 0), only a NaN makes l one, and m = -inf is left to mark the merge's
+    // dead pieces, so that a cut gives what one wave gives
     AttnState<D> st;
     auto reset = [&]() {
 #pragma unroll
         for (int t = 0; t < NT; ++t) st.o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        st.m = -INFINITY;
+        st.m = -__FLT_MAX__;
         st.l = 0.f;
     };
     reset();
@@ -1280,7 +1283,8 @@ struct MergeAcc {
         }
     }
     // a dead piece (past the last one, or of an empty share) has m = -inf:
-    // weight 0, its values unused
+    // weight 0, its values unused (a piece of -inf scores alone has l = 0, one
+    // with a NaN a NaN l, both at a finite m)
     template <int K>
     __device__ __forceinline__ void fold(const float2 (&ml)[K][NK], const f32x4 (&o)[K][NK]) {
 #pragma unroll

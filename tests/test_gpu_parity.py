@@ -358,6 +358,32 @@ def test_shares_left_empty_by_extreme_weights():
     G.assert_close(got, oracle_case(case, scale), "bf16", "weights 511 : 1")
 
 
+def test_nan_and_inf_shares_as_uncut():
+    # keys of whole shares that are NaN in KV head 0, and over bf16 pools
+    # score -inf in KV head 1: every cut gives what one wave gives (a NaN row
+    # is NaN, a weight of -inf is 0 as the oracle has it), through both merges
+    for B, lens in ((1, [6000]), (24, [6000] * 24)):
+        for kv in ("bf16", "fp8"):
+            rng = np.random.default_rng(B)
+            case = dn.random_case(rng, B, 4, 2, 128, lens, kv)
+            scale = float(np.float32(1.0 / np.sqrt(128)))
+            d = dev_case(case, kv)
+            d["q"][:, 2:, 0] = 1.0
+            case["q_bits"] = G.bits16(d["q"])
+            pages = torch.cat([d["bt"][:, lo:hi].reshape(-1) for lo, hi in ((0, 60), (128, 256))]).long()
+            if kv == "fp8":
+                d["k"][pages, 0] = 0x7F
+            else:
+                d["k"][pages, 0] = float("nan")
+                d["k"][pages, 1, 0, :, 0] = -float("inf")
+            case["k_pages"] = G.host_codes(d["k"], kv)
+            ref = oracle_case(case, scale, kv)
+            for waves in (1, 0, 37, 300):
+                got = run_case(d, scale, max_waves=waves)
+                assert np.isnan(got[:, :2]).all(), (B, kv, waves)
+                G.assert_close(got[:, 2:], ref[:, 2:], kv, f"-inf shares B={B} {kv} waves={waves}")
+
+
 @pytest.mark.parametrize("B,kv", [(2500, "bf16"), (8192, "fp8")])
 def test_large_batches_of_short_requests(B, kv):
     # more than 1024 requests: every attention wave reads the lengths in
