@@ -324,7 +324,8 @@ int bellman_kv_write(const bellman_tensor_t *k_new, const bellman_tensor_t *v_ne
  * and its bookkeeping, B ceil(maxP / 4) (4 + 4 H_kv + 128 D H_kv) +
  * 4 (B + 1) bytes more (maxP = the block table's width); and where keys are
  * shared out 128 (4 D + 8) bytes a share, at most four shares a CU (a capture
- * with no room for those runs uncut; results agree within rounding).  Like
+ * with no room for those, or a call whose device has no memory for them, runs
+ * uncut; results agree within rounding).  Like
  * bellman_kv_write, once the workspace has grown to the call's size the call
  * enqueues only kernels (graph-capturable). */
 int bellman_prefill_attention(const bellman_tensor_t *q, const bellman_tensor_t *k_pages,
@@ -626,7 +627,9 @@ const char *bellman_last_error(void);
 
 /* Make sure the current device's workspace holds at least `bytes`
  * (hipMalloc outside any timed region or graph capture; a smaller block it
- * replaces stays allocated until bellman_shutdown). */
+ * replaces stays allocated until bellman_shutdown).  The block is taken with
+ * room to grow, a quarter or, if that is more, 3 `bytes` up to 256 MiB; where
+ * the device has no memory for that, `bytes` rounded up to 1 MiB. */
 int bellman_reserve_workspace(int64_t bytes);
 
 /* Synchronise `stream`, copy the current device's error word to *flags and

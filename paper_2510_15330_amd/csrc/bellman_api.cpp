@@ -74,8 +74,11 @@ int cu_count(int dev) {
 }
 
 // Grow the current device's workspace to at least `bytes` (no region of it
-// needs initialising).
-int ensure_workspace(int dev, size_t bytes, hipStream_t stream, char** base) {
+// needs initialising), with room to grow: a quarter, or for prompt calls and
+// reservations (`prompt`) up to fourfold on small blocks, so that the tile
+// padding of narrow tables' value copies fits what other shapes have reserved.
+// Where the device has no memory for the room, `bytes` alone must do.
+int ensure_workspace(int dev, size_t bytes, hipStream_t stream, char** base, bool prompt) {
     std::lock_guard<std::mutex> lock(g_ws_mutex);
     Workspace& w = g_ws[dev];
     if (bytes < kWsHeader) bytes = kWsHeader;
@@ -87,16 +90,17 @@ int ensure_workspace(int dev, size_t bytes, hipStream_t stream, char** base) {
             return fail(BELLMAN_ERR_UNSUPPORTED,
                         "the workspace would have to grow to %zu bytes during graph capture; make the same call, "
                         "or bellman_reserve_workspace, before capturing", bytes);
-        // room to grow: small blocks fourfold, so that the tile padding of
-        // narrow tables' value copies fits what other shapes have reserved
-        size_t want = bytes + std::max(bytes / 4, std::min(3 * bytes, (size_t)256 << 20));
-        want = (want + 0xFFFFF) & ~(size_t)0xFFFFF;
+        const size_t room = std::max(bytes / 4, prompt ? std::min(3 * bytes, (size_t)256 << 20) : 0);
+        size_t want = 0;
         void* p = nullptr;
-        e = hipMalloc(&p, want);
-        if (e != hipSuccess) {
+        for (const size_t size : {bytes + room, bytes}) {
+            want = (size + 0xFFFFF) & ~(size_t)0xFFFFF;
+            e = hipMalloc(&p, want);
+            if (e == hipSuccess) break;
             (void)hipGetLastError();
-            return fail(BELLMAN_ERR_OOM, "workspace hipMalloc(%zu): %s", want, hipGetErrorString(e));
         }
+        if (e != hipSuccess)
+            return fail(BELLMAN_ERR_OOM, "workspace hipMalloc(%zu): %s", want, hipGetErrorString(e));
         if (w.base) w.retired.push_back(w.base);
         w.base = (char*)p;
         w.cap = want;
@@ -390,7 +394,7 @@ int decode_attention(const bellman_tensor_t* q, const bellman_tensor_t* k_pages,
                         "(2 * waves * G partial slots of %zu bytes)",
                         total, kScratchBytes, sizeof(float2) + sizeof(float) * (size_t)ps.D);
         if ((rc = device_scratch(dev, &base))) return rc;
-    } else if ((rc = ensure_workspace(dev, total, s, &base))) {
+    } else if ((rc = ensure_workspace(dev, total, s, &base, false))) {
         return rc;
     }
     int32_t* err;
@@ -481,7 +485,7 @@ int bellman_reserve_workspace(int64_t bytes) {
     int dev, rc;
     if ((rc = current_device(&dev))) return rc;
     char* base;
-    return ensure_workspace(dev, (size_t)bytes, nullptr, &base);
+    return ensure_workspace(dev, (size_t)bytes, nullptr, &base, true);
 }
 
 void bellman_shutdown(void) {
@@ -667,7 +671,7 @@ int bellman_kv_write(const bellman_tensor_t* k_new, const bellman_tensor_t* v_ne
     int dev;
     if ((rc = current_device(&dev))) return rc;
     char* base;
-    if ((rc = ensure_workspace(dev, kWsHeader + align256((size_t)(B + 1) * 4), (hipStream_t)stream, &base)))
+    if ((rc = ensure_workspace(dev, kWsHeader + align256((size_t)(B + 1) * 4), (hipStream_t)stream, &base, false)))
         return rc;
     int32_t* err;
     if ((rc = device_error_word(dev, &err))) return rc;
@@ -762,19 +766,22 @@ int bellman_prefill_attention_opts(const bellman_tensor_t* q, const bellman_tens
     const size_t off_ml = off_copy + align256(ps.fp8 ? 0 : max_steps * ps.H_kv * 4 * page_head_bytes);
     const size_t piece_rows = a.split ? (size_t)a.max_units * kPrefillRows : 0;
     const size_t off_o = off_ml + align256(piece_rows * sizeof(float2));
-    size_t total = off_o + align256(piece_rows * ps.D * sizeof(float));
+    const size_t total = off_o + align256(piece_rows * ps.D * sizeof(float));
 
     hipStream_t s = (hipStream_t)stream;
     // The pieces grow with the call's tokens, the rest only with the batch
     // and the table: a capture of more tokens than the calls before it had
-    // runs uncut where the pieces would not fit.
-    if (a.split && capture_short_of(dev, total, s)) {
+    // runs uncut where the pieces would not fit, and so does a call for whose
+    // pieces the device has no memory.
+    char* base;
+    rc = a.split && capture_short_of(dev, total, s) ? BELLMAN_ERR_OOM : ensure_workspace(dev, total, s, &base, true);
+    if (rc == BELLMAN_ERR_OOM && a.split) {
         a.split = 0;
         a.max_units = a.max_tiles;
-        total = off_ml;
+        g_last_error[0] = 0;
+        rc = ensure_workspace(dev, off_ml, s, &base, true);
     }
-    char* base;
-    if ((rc = ensure_workspace(dev, total, s, &base))) return rc;
+    if (rc) return rc;
     int32_t* err;
     if ((rc = device_error_word(dev, &err))) return rc;
     a.q = (const uint16_t*)q->data;
