@@ -150,18 +150,21 @@ int bellman_decode_attention(const bellman_tensor_t *q, const bellman_tensor_t *
                              bellman_tensor_t *out, void *stream);
 
 typedef struct bellman_attn_opts {
-    int32_t max_waves;    /* cap on the waves that share the work; 0 = one
-                             workgroup of four waves per CU where pages_per_step
-                             and pipeline_depth are 0 too, else every wave the GPU
-                             can keep resident.  Fewer waves split fewer
+    int32_t max_waves;    /* cap on the waves that share the work; 0 = every wave
+                             the GPU can keep resident, but where pages_per_step
+                             and pipeline_depth are 0 too one workgroup of four
+                             waves per CU over bf16 pools, and one or two by the
+                             call's shape over fp8 pools.  Fewer waves split fewer
                              requests (results agree within rounding). */
     int32_t xcd_skew;     /* share weights of the waves of even- and odd-numbered
                              XCDs (workgroup i runs on XCD i mod 8), applied only
                              when every wave gets at least 384 pages (steps x
                              pages per step):
                              0 = the library's choice (on a whole 256-CU device
-                             k = 10 over bf16 pools, k = 6 with two workgroups
-                             per CU; equal shares otherwise); -1 = equal shares; k in
+                             k = 10 over bf16 pools with one workgroup per CU,
+                             k = 6 with more and over fp8 pools; equal shares
+                             over fp8 pools with one workgroup and more than 8
+                             query heads a KV head); -1 = equal shares; k in
                              1..255 = weights 256 + k : 256 - k.  Results agree
                              within rounding. */
     int32_t pages_per_step; /* 16-token pages per softmax update: 1 or 2 (bf16),
@@ -181,7 +184,8 @@ typedef struct bellman_attn_opts {
     void *event_end;      /* optional hipEvent_t recorded right after it (before the
                              merge of the cut requests) */
     int64_t *wave_times;  /* optional device array of 3 * W int64 (W = the waves the
-                             call uses: every resident wave, or max_waves): wave w
+                             call uses: at most every wave the GPU can keep
+                             resident, or max_waves): wave w
                              writes [3w] = the 100 MHz real-time clock when it
                              starts, [3w+1] = the clock when it has written its
                              last result, [3w+2] = (XCD id << 32) | HW_ID of its

@@ -34,11 +34,15 @@ int fail(int code, const char* fmt, ...) {
 // ------------------------------------------------------------- workspace ---
 
 constexpr int kXcdSkew = 10;          // share weights 266 : 246, even : odd XCDs (bf16; measured best of 0-28)
-constexpr int kXcdSkew2 = 6;          // the same with two workgroups per CU (fp8 stress batch: best of 0, 6, 12, 20);
-                                      // fp8 with one: equal shares (400 requests of 3-5k tokens 510 us, 516-519 at 6-14)
+constexpr int kXcdSkew2 = 6;          // the same with two workgroups per CU (fp8 stress batch: best of 0, 6, 12, 20),
+                                      // and fp8 with one at up to 8 heads a KV head: equal shares / 6 / 10 on 400
+                                      // requests of 3-5k tokens 509 / 505 / 503 us, 256 of 6-13.5k 780 / 771 / 774, 512
+                                      // with Zipf lengths to 32k 693 / 690 / 696; at 16 heads equal: 556 / 559 / 563,
+                                      // 798 / 804 / 809, 713 / 713 / 720
 constexpr int kMaxAttnBatch = 8192;  // lengths every attention wave reads to find its share
 constexpr double kShortSharePages = 512;   // below this many table pages a wave: short shares (see their use)
 constexpr double kShortSharePages64 = 64;  // the same for depth 1 at head_dim 64
+constexpr double kWideTablePages = 4096;   // fp8: from this many on, two workgroups a CU (see their use)
 
 // The growable per-device workspace.  Growing it allocates a larger block
 // and keeps the old one alive until bellman_shutdown, so kernels already
@@ -355,20 +359,39 @@ int decode_attention(const bellman_tensor_t* q, const bellman_tensor_t* k_pages,
         return fail(BELLMAN_ERR_UNSUPPORTED,
                     "wave_times: traced kernels are built for head_dim 128 at the default steps only");
     if (wave_times && !aligned(wave_times, 8)) return fail(BELLMAN_ERR_UNSUPPORTED, "wave_times must be 8-byte aligned");
-    int& bpc = g_blocks_per_cu[dev][ps.fp8][ps.D == 128][pps][depth];
-    if (bpc == 0) {
-        bpc = attention_blocks_per_cu(pps, depth, ps.fp8, ps.D);
-        if (depth == 2) bpc = 1;  // one wavefront per SIMD
+    int& cached = g_blocks_per_cu[dev][ps.fp8][ps.D == 128][pps][depth];
+    if (cached == 0) {
+        // one wavefront per SIMD at depth 2; at depth 1 as many as fit, up to
+        // a bound: whether a third workgroup of the fp8 default step fits at
+        // head_dim 64 hangs on one register of a compilation (167 or 169), and
+        // it costs (512 requests with Zipf lengths 342 us against 312)
+        const int fit = attention_blocks_per_cu(pps, depth, ps.fp8, ps.D);
+        cached = depth == 2 ? 1 : std::min(fit, pps == 4 ? 2 : 4);
     }
+    const int bpc = cached;
     // Every resident wave takes an equal share of the flattened step stream;
-    // the library's own steps run one workgroup a CU.  Over fp8 pools two fit,
-    // but the second one's waves cost more (twice the plans, ramps, segment
-    // ends and partial pieces, and a memory system that streams fewer waves
-    // faster) than they hide.  Calls, two workgroups / one with equal shares:
-    // 32 requests of 0.5-8k tokens 56.8 / 50.6 us, 64 of 1-4k 67.4 / 64.3, 64
-    // of 1-4k at head_dim 64 48.3 / 41.3, 400 of 3-5k 541 / 510, 512 with Zipf
-    // lengths to 16k 437 / 431.
-    const int wgs = chosen ? 1 : bpc;
+    // the library's own steps run one workgroup a CU.  Over fp8 pools two fit.
+    // At head_dim 128 the second one's waves cost more (twice the plans, ramps,
+    // segment ends and partial pieces, and a memory system that streams fewer
+    // waves faster) than they hide: calls with two workgroups / one, at 4
+    // query heads a KV head, 32 requests of 0.5-8k tokens 62.0 / 55.0 us, 64
+    // of 1-4k 71.8 / 66.3, 400 of 3-5k 514 / 504, 256 of 6-13.5k 767 / 757.
+    // The widest tables mostly mean lengths that differ much, where shares of
+    // many short requests take longer than shares of long ones and the second
+    // workgroup evens that out at up to 4 heads (1024 with Zipf lengths to 16k,
+    // 1 head 770 / 788, 2 heads 785 / 796, 4 heads 811 / 815, 8 heads 845 / 848,
+    // 16 heads 912 / 892); a table of that width over even lengths pays for it
+    // (600 of 3-5k 759 / 750).
+    // At head_dim 64 a step has half the bytes to hide as much arithmetic
+    // behind, and two win from short shares on, later the more heads there are
+    // (512 with Zipf lengths to 32k 321 / 375 us at 4 heads, 352 / 378 at 16;
+    // 64 of 1-4k 39.0 / 41.5, 41.5 / 43.0 at 8 heads, 43.4 / 42.7 at 16; 20 of
+    // 0.5-8k, 77 table pages a wave, 26.9 / 26.2, 28 of them, 108 pages, 31.2 /
+    // 31.4 at 4 heads and 34.6 / 32.4 at 8).
+    const bool two = chosen && ps.fp8 &&
+                     (ps.D == 64 ? table_pages_per_wave >= std::max(96.0, 14.0 * (double)G)
+                                 : G <= 4 && table_pages_per_wave >= kWideTablePages);
+    const int wgs = chosen && !two ? 1 : bpc;
     const int64_t cu_waves = (int64_t)g_cu_count[dev] * (kAttnBlock / kWaveSize);
     int64_t waves = cu_waves * wgs, sized = cu_waves * (depth == asked_depth ? bpc : 1);
     if (max_waves > 0 && waves > max_waves) waves = max_waves;
@@ -427,7 +450,8 @@ int decode_attention(const bellman_tensor_t* q, const bellman_tensor_t* k_pages,
     // The default XCD weights were measured on a whole MI355X (256 CUs,
     // workgroup i on XCD i mod 8), with one and with two workgroups per CU;
     // partitioned devices keep equal shares.
-    if (skew_opt == 0) a.skew = g_cu_count[dev] != 256 ? 0 : wgs == 2 ? kXcdSkew2 : ps.fp8 ? 0 : kXcdSkew;
+    if (skew_opt == 0)
+        a.skew = g_cu_count[dev] != 256 ? 0 : wgs == 1 && !ps.fp8 ? kXcdSkew : wgs > 1 || G <= 8 ? kXcdSkew2 : 0;
     else a.skew = skew_opt < 0 ? 0 : skew_opt;
     a.err = err;
     a.cuts = (int4*)(base + off_cuts);

@@ -358,6 +358,27 @@ def test_shares_left_empty_by_extreme_weights():
     G.assert_close(got, oracle_case(case, scale), "bf16", "weights 511 : 1")
 
 
+@pytest.mark.parametrize("Hq,D,edge", [(2, 64, 96), (18, 64, 126), (32, 64, 224), (8, 128, 4096), (10, 128, 4096)])
+def test_fp8_workgroups_on_both_sides_of_the_rule(Hq, D, edge):
+    # one workgroup a CU or two, by the table's pages a wave: the same results
+    # within the bound on both sides of the line, and with empty columns
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    B, Hkv = 8, 2
+    rng = np.random.default_rng(Hq + D)
+    case = dn.random_case(rng, B, Hq, Hkv, D, [1, 0, 17, 900, 64, 2000, 333, 16], "fp8")
+    # values below 8: from there on the output's own rounding to bf16 (2^-9 of
+    # it, 0.031 at the value of one token) is over the bound on the largest error
+    case["v_scale"] = (rng.uniform(0.5, 1.5, size=(B, Hkv)) * (5 / 448)).astype(np.float32)
+    scale = float(np.float32(1.0 / np.sqrt(D)))
+    ref = oracle_case(case, scale, "fp8")
+    for width in (edge * 4 * cus // (B * Hkv) - 1, edge * 4 * cus // (B * Hkv)):
+        d = dev_case(case, "fp8")
+        d["bt"] = torch.nn.functional.pad(d["bt"], (0, width - d["bt"].shape[1]), value=-1)
+        got = run_case(d, scale)
+        assert bl.device_errors() == 0
+        G.assert_close(got, ref, "fp8", f"D={D} G={Hq // Hkv} width={width}")
+
+
 def test_nan_and_inf_shares_as_uncut():
     # keys of whole shares that are NaN in KV head 0, and over bf16 pools
     # score -inf in KV head 1: every cut gives what one wave gives (a NaN row

@@ -50,6 +50,28 @@ def test_traced_kernel_same_bits_and_records(name, pps, waves):
     assert bl.device_errors() == 0
 
 
+@pytest.mark.parametrize("H_q", [8, 16, 32])          # 2, 4 and 8 query heads a KV head
+def test_fp8_workgroups_by_table_width(H_q):
+    # fp8 at head_dim 128: one workgroup a CU, two over a table of 4096 pages a
+    # wave or more at up to 4 heads; the options' own steps take two
+    cus, B, H_kv = torch.cuda.get_device_properties(0).multi_processor_count, 4, 4
+    g = torch.Generator(device="cuda").manual_seed(1)
+    pages = torch.randint(0, 120, (2, 64, H_kv, 128 * 16), generator=g, dtype=torch.uint8, device="cuda")
+    q = torch.randn((B, H_q, 128), generator=g, device="cuda").to(torch.bfloat16)
+    scale = torch.full((B, H_kv), 0.01, device="cuda")
+    lens = torch.full((B,), 200, dtype=torch.int32, device="cuda")
+    edge = 4096 * 4 * cus // (B * H_kv)
+    for width, kw, want in ((edge - 1, {}, 1), (edge, {}, 2 if H_q <= 16 else 1),
+                            (13, dict(pages_per_step=4, pipeline_depth=1), 2)):
+        bt = torch.full((B, width), -1, dtype=torch.int32, device="cuda")
+        bt[:, :13] = torch.arange(B * 13, device="cuda").view(B, 13)
+        rec = torch.full((3 * 16384,), -1, dtype=torch.int64, device="cuda")
+        bl.decode_attention(q, pages[0].view(64, H_kv, 8, 16, 16), pages[1].view(64, H_kv, 128, 16), bt, lens, 0.1,
+                            torch.empty_like(q), k_scale=scale, v_scale=scale, wave_times=rec, **kw)
+        assert bl.device_errors() == 0
+        assert int((rec.view(-1, 3)[:, 0] >= 0).sum()) == want * 4 * cus, (width, kw)
+
+
 def test_trace_rejects_untraced_shapes():
     w = G.to_device(wl.build("tiny", seed=0))          # head_dim 64: no traced twin
     out = torch.empty((w.B, w.H_q, w.D), dtype=torch.bfloat16, device="cuda")

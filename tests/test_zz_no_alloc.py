@@ -101,3 +101,19 @@ def test_noalloc_rejects_calls_beyond_the_array():
     got = _run(bl.decode_attention_noalloc, d, scale, max_waves=1900)
     want = _run(bl.decode_attention, d, scale, max_waves=1900)
     assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+def test_noalloc_takes_what_four_workgroups_a_cu_need():
+    # one page a step, one step ahead, head_dim 64: registers leave room for
+    # five workgroups a CU, but 14 heads' slots for the waves of five are over
+    # the array (the waves of four are 30 MB)
+    rng = np.random.default_rng(779)
+    case = dn.random_case(rng, 3, 28, 2, 64, [5000, 70, 1], "bf16")
+    d = _dev(case, "bf16")
+    kw = dict(pages_per_step=1, pipeline_depth=1)
+    got = _run(bl.decode_attention_noalloc, d, 0.125, **kw)
+    want = _run(bl.decode_attention, d, 0.125, **kw)
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    ref = oracle.decode_attention(case["q_bits"], case["k_pages"], case["v_pages"], case["block_table"],
+                                  case["seq_lens"], 0.125, G.kv_code("bf16"), None, None)
+    G.assert_close(G.out_f64(got), ref, "bf16", "noalloc, four workgroups a CU")
