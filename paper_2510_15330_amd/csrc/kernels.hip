@@ -1565,10 +1565,19 @@ int attention_blocks_per_cu(int pages_per_step, int depth, bool fp8, int D) {
 // against 3.9 us; 48 requests of 6-13.5k (96 over 1024 waves: 11 pieces a
 // cut) 5.1 against 5.0 us; 32 requests over fp8 pools (256 over 2048 waves: 8
 // pieces) 6.6 against 8.8 us, where the larger workgroups' launch shows.
-constexpr int kLongMergePieces = 16;
+// Pieces of more than 256 float4s (over 8 heads at head_dim 128) cost a single
+// wave eight loads each and fill its registers with four of them: those are
+// dealt from 2 pieces a cut on, unless the table has room for fewer than four
+// steps (calls at 16 heads over 4 KV heads, one wave a cut / a workgroup a
+// cut: 32 requests of 200-600 tokens 25.7 / 17.5 us, 64 of them 26.7 / 21.2,
+// 128 of them 35.7 / 35.2, 32 of 1-2k 34.7 / 27.5; two steps, 32 of 60-120
+// over fp8 pools, 14.8 / 15.5).
+constexpr int kLongMergePieces = 16, kLongMergeWide = 2;
 void launch_merge(const AttnArgs& a, hipStream_t s) {
     const bool d128 = a.D == 128;
-    if ((int64_t)a.B * a.H_kv * kLongMergePieces <= a.waves) {
+    const int64_t cuts = (int64_t)a.B * a.H_kv;
+    if (cuts * kLongMergePieces <= a.waves ||
+        (a.G * a.D > 1024 && cuts * kLongMergeWide <= a.waves && a.max_pages > 3 * a.pp)) {
         const int R = (a.waves + 255) / 256;     // <= 64 records: at most kMaxWaves waves
         const dim3 g((a.waves + R - 1) / R), blk(kLongWaves * kWaveSize);
         if (d128) hipLaunchKernelGGL((merge_long_kernel<128>), g, blk, 0, s, a, R);

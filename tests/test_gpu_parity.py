@@ -327,6 +327,8 @@ def test_long_shares_with_weighted_split(kv, pps, depth):
     (2, 7, 1, 128, [2500, 9], "bf16"),           # pieces of 3.5 slices
     (3, 2, 1, 64, [300, 1, 700], "bf16"),        # a piece of half a slice; fewer units than waves
     (1, 8, 1, 128, [20000], "fp8"),
+    (24, 64, 4, 128, [100 + 37 * i for i in range(24)], "bf16"),   # pieces of over 256 float4s: from 2 a cut on
+    (24, 36, 4, 128, [100 + 37 * i for i in range(24)], "fp8"),
 ])
 def test_requests_cut_over_many_waves(B, Hq, Hkv, D, lens, kv):
     # few (request, head)s, each cut over 8 waves' ranges or more: the merge
