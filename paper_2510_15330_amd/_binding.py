@@ -3,18 +3,21 @@
 The device calls go through the ``_marshal`` extension, which reads plain
 device tensors in native code; what it leaves (other types, host tensors)
 takes the ctypes path here, which raises the errors.  Everything else is
-ctypes."""
+ctypes, and so are the device calls where the extension is not built."""
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import math
 import os
+import warnings
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # BELLMAN_LIBRARY selects another build of the same library (the host
-# sanitizer build of paper_2510_15330_amd/build.py --sanitize)
+# sanitizer build of paper_2510_15330_amd/build.py --sanitize), with the
+# _marshal.so beside it
 _LIB_PATH = os.environ.get("BELLMAN_LIBRARY") or os.path.join(_HERE, "libbellman.so")
 
 BF16, FP8_E4M3FN, INT32, FP32 = 1, 2, 3, 4
@@ -87,7 +90,8 @@ class LoadSignal(ctypes.Structure):
 
 
 _lib = None
-_native = None          # _marshal.call
+_native = None          # _marshal.call, or None
+_warned = False         # that it is None
 _addr = {}              # entry point -> its address, for _marshal.call
 
 # the forms of call (marshal.cpp)
@@ -98,15 +102,27 @@ def library_path() -> str:
     return _LIB_PATH
 
 
+def _load_marshal():
+    """The _marshal extension beside the library, set up, or None."""
+    path = os.path.join(os.path.dirname(os.path.abspath(_LIB_PATH)), "_marshal.so")
+    if not os.path.exists(path):
+        return None
+    try:
+        spec = importlib.util.spec_from_file_location(__package__ + "._marshal", path)
+        m = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(m)
+        m.setup(torch.Tensor, torch.nn.Parameter, tuple(_DTYPES.items()), torch.float32,
+                torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+    except (ImportError, AttributeError):   # built for another Python; a torch without devices
+        return None
+    return m
+
+
 def library():
     """Load libbellman.so (built in-tree); raise if it is missing."""
     global _lib, _native
     if _lib is not None:
         return _lib
-    try:
-        from . import _marshal
-    except ImportError as e:
-        raise RuntimeError(f"the _marshal extension is not built ({e}); run __graft_entry__.build() first") from e
     if not os.path.exists(_LIB_PATH):
         raise RuntimeError(f"{_LIB_PATH} is not built; run __graft_entry__.build() "
                            "(hipcc, gfx950) first — there is no fallback path")
@@ -167,9 +183,8 @@ def library():
     for name in ("kv_append", "decode_attention", "decode_attention_noalloc", "decode_step", "kv_write",
                  "prefill_attention"):
         _addr[name] = ctypes.cast(getattr(lib, "bellman_" + name), P).value
-    _marshal.setup(torch.Tensor, torch.nn.Parameter, tuple(_DTYPES.items()), torch.float32,
-                   torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
-    _native = _marshal.call
+    marshal = _load_marshal()
+    _native = None if marshal is None else marshal.call
     _lib = lib
     return lib
 
@@ -231,8 +246,14 @@ def _stream(stream):
 def _call(name, form, stream, scale, opts, k_scale, v_scale, *tensors):
     """The native path: True if it made the call, False if it is not a case
     for it (nothing was done)."""
+    global _warned
     if _native is None:
         library()
+        if _native is None:
+            if not _warned:
+                _warned = True
+                warnings.warn("_marshal.so is not built for this Python: device calls take ctypes' longer host time")
+            return False
     st = None if stream is None else _stream(stream).value or 0
     rc = _native(_addr[name], form, st, scale, opts, k_scale, v_scale, *tensors)
     if rc is None:

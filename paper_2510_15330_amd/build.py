@@ -1,4 +1,5 @@
-"""Build libbellman.so (hipcc, gfx950) and the _marshal extension (g++) in-tree.
+"""Build libbellman.so (hipcc, gfx950) and the _marshal extension in-tree (without
+Python's headers only the library: the binding then calls it through ctypes).
 
 ``python -m paper_2510_15330_amd.build --sanitize OUT.so`` builds the same
 library with the host code of its C++ sources (descriptor validation,
@@ -70,15 +71,24 @@ def _build(out: str, sanitize: bool, verbose: bool) -> str:
     return out
 
 
-def _build_marshal(verbose: bool) -> None:
-    tmp = MARSHAL + f".tmp{os.getpid()}"
-    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
-          os.path.join(CSRC, "marshal.cpp"), "-o", tmp], verbose)
-    os.replace(tmp, MARSHAL)
+def _build_marshal(out: str, sanitize: bool, verbose: bool) -> None:
+    """The _marshal extension (host code) at `out`; nothing there without Python's headers."""
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        print(f"no Python.h in {include}: _marshal is not built", file=sys.stderr)
+        if os.path.exists(out):
+            os.remove(out)
+        return
+    tmp = out + f".tmp{os.getpid()}"
+    flags = SANITIZE_FLAGS + ["-shared-libsan"] if sanitize else []
+    _run([hipcc(), "-x", "hip", "--offload-host-only", "-no-hip-rt", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+          "-Wno-unused-command-line-argument", *flags, "-I" + include, os.path.join(CSRC, "marshal.cpp"), "-o", tmp],
+         verbose)
+    os.replace(tmp, out)
 
 
 def build(verbose: bool = False) -> str:
-    _build_marshal(verbose)
+    _build_marshal(MARSHAL, False, verbose)
     tmp = LIB + f".tmp{os.getpid()}"
     _build(tmp, False, verbose)
     os.replace(tmp, LIB)
@@ -86,7 +96,9 @@ def build(verbose: bool = False) -> str:
 
 
 def build_sanitized(out: str, verbose: bool = False) -> str:
-    """The library with its C++ host sources under ASan + UBSan, at `out`."""
+    """The library with its C++ host sources under ASan + UBSan at `out`, and
+    the _marshal extension under them beside it."""
+    _build_marshal(os.path.join(os.path.dirname(os.path.abspath(out)), "_marshal.so"), True, verbose)
     return _build(out, True, verbose)
 
 

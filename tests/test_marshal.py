@@ -4,6 +4,10 @@ and what it does not take it leaves to the general path untouched."""
 from __future__ import annotations
 
 import ctypes
+import os
+import shutil
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -47,6 +51,36 @@ def test_host_tensors_and_other_objects_are_left():
         B._native(addr, B._APPEND, 0, 0.0, 0, None, None, t)
     with pytest.raises(TypeError):
         B._native(addr, 99, 0, 0.0, 0, None, None, *[t] * 6)
+
+
+@pytest.mark.parametrize("beside", ["nothing", "no extension"])
+def test_library_without_the_extension(tmp_path, beside):
+    # the library alone: host calls work, device calls keep the general path
+    # and its errors
+    B.library()
+    lib = str(tmp_path / "libbellman.so")
+    shutil.copy(B.library_path(), lib)
+    if beside != "nothing":
+        (tmp_path / "_marshal.so").write_bytes(b"not a library")
+    code = """
+import warnings, torch, paper_2510_15330_amd as bl
+assert bl.version()
+t = torch.zeros(2, 2)
+with warnings.catch_warnings(record=True) as w:
+    warnings.simplefilter("always")
+    for _ in range(2):
+        try:
+            bl.kv_append(t, t, t, t, t, t)
+        except ValueError as e:
+            assert "device tensors" in str(e)
+        else:
+            raise AssertionError("accepted")
+assert [x for x in w if "_marshal" in str(x.message)].__len__() == 1
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, env=dict(os.environ, BELLMAN_LIBRARY=lib),
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
 
 
 @pytest.mark.gpu

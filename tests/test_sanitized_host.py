@@ -1,6 +1,6 @@
 """The host code under AddressSanitizer and UndefinedBehaviorSanitizer: the
 library's C++ sources (descriptor validation, workspace bookkeeping,
-controllers, serving model) and the oracle are rebuilt with the sanitizers
+controllers, serving model), the binding's marshalling and the oracle are rebuilt with the sanitizers
 (paper_2510_15330_amd/build.py --sanitize, oracle.build_sanitized) and the CPU
 tests that drive native code run against those builds in a child process,
 which aborts on the first report.  No GPU is used (GPU sanitizers are not)."""
@@ -14,7 +14,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 NATIVE_TESTS = ["tests/test_abi.py", "tests/test_controller_lib.py", "tests/test_controller_variants_lib.py",
-                "tests/test_serve_sim.py", "tests/test_oracle_pins.py", "tests/test_oracle_prefill.py",
+                "tests/test_serve_sim.py", "tests/test_marshal.py", "tests/test_oracle_pins.py", "tests/test_oracle_prefill.py",
                 "tests/test_oracle_quant.py"]
 
 pytestmark = pytest.mark.skipif(os.environ.get("BELLMAN_SANITIZED_RUN") == "1", reason="inside the sanitized run")
@@ -39,7 +39,8 @@ def test_native_tests_clean_under_asan_and_ubsan(tmp_path):
     # the child really loads the sanitized builds
     probe = ("import paper_2510_15330_amd as bl, oracle; bl.library(); oracle.load(); "
              "m = open('/proc/self/maps').read(); "
-             f"assert {lib!r} in m and {olib!r} in m and 'libclang_rt.asan' in m; print('loaded')")
+             f"assert {lib!r} in m and {str(tmp_path / '_marshal.so')!r} in m and {olib!r} in m; "
+             "assert 'libclang_rt.asan' in m; print('loaded')")
     r = subprocess.run([sys.executable, "-c", probe], cwd=ROOT, env=env, capture_output=True, text=True)
     assert r.returncode == 0 and "loaded" in r.stdout, r.stdout[-2000:] + r.stderr[-2000:]
     r = subprocess.run([sys.executable, "-m", "pytest", "-q", "-x", "-m", "not gpu", "-p", "no:cacheprovider"]
