@@ -726,55 +726,55 @@ __device__ __forceinline__ int attn_len(const AttnArgs& a, int L) {
 // Decode step: request b's new K and V rows of KV head g, to be written at
 // position L (the stored length) by the whole wave, as kv_append_kernel
 // does: K as 16-byte chunks (lanes 0 .. D/X - 1), V as D / 64 consecutive
-// dims a lane; fp8 pools take codes as they are or bf16 rows quantised with
-// the (request, head)'s scales.  row_load issues every read (block-table
-// entry, rows, scales) at once; row_store writes them, skipping a position
-// outside the pool (the merge pass flags it).
+// dims a lane; fp8 pools take codes as they are or bf16 rows quantised (QUANT)
+// with the (request, head)'s scales.  row_load issues every read (block-table
+// entry, rows, scales) at once, all without branches and none into scalar
+// registers, so that they stay in flight until row_store; it writes them,
+// skipping a position outside the pool (the merge pass flags it).
 struct NewRow {
-    int pg, slot, g;
+    int pg;          // the page, in a vector register
+    int slot, g;     // slot -1: nothing to store
     u32x4 w, h;      // K chunk (and its second half when quantising)
     uint32_t vv;     // this lane's V dims
     float ks, vs;    // quantising scales
 };
 
-template <int D, bool FP8>
-__device__ __forceinline__ NewRow row_load(const AttnArgs& a, int b, int g, int L, int lane) {
+// zero: 0 in a vector register, unknown to the compiler
+template <int D, bool FP8, bool QUANT>
+__device__ __forceinline__ void row_load(NewRow& r, const AttnArgs& a, int b, int g, int L, int lane, int zero) {
     constexpr int EB = FP8 ? 1 : 2;
     constexpr int X = 16 / EB;                   // pool elements per K chunk
     constexpr int VD = D / 64;                   // V dims a lane
-    NewRow r;
-    r.pg = a.block_table[(int64_t)b * a.bt_stride + (L >> 4)];
+    constexpr int SB = QUANT ? 2 : EB;           // source element bytes
+    r.pg = a.block_table[(int64_t)b * a.bt_stride + (L >> 4) + zero];
     r.slot = L & (kPage - 1);
     r.g = g;
-    const bool quant = FP8 && a.quant;
-    const int SB = quant ? 2 : EB;               // source element bytes
     const char* kn = (const char*)a.k_new + ((int64_t)b * a.new_sb + (int64_t)g * a.new_sh) * SB;
     const char* vn = (const char*)a.v_new + ((int64_t)b * a.vnew_sb + (int64_t)g * a.vnew_sh) * SB;
-    r.w = u32x4{0u, 0u, 0u, 0u};
-    r.h = u32x4{0u, 0u, 0u, 0u};
-    if (lane < D / X) {
-        r.w = *(const u32x4*)(kn + (int64_t)lane * X * SB);
-        if (quant) r.h = *(const u32x4*)(kn + (int64_t)lane * X * SB + 16);
+    const int c = min(lane, D / X - 1);          // lanes past the chunks read the last one again
+    r.w = *(const u32x4*)(kn + (int64_t)c * X * SB);
+    if constexpr (QUANT) r.h = *(const u32x4*)(kn + (int64_t)c * X * SB + 16);
+    if constexpr (QUANT || EB == 2)
+        r.vv = VD == 2 ? *(const uint32_t*)(vn + (int64_t)lane * 4) : *(const uint16_t*)(vn + (int64_t)lane * 2);
+    else
+        r.vv = VD == 2 ? *(const uint16_t*)(vn + (int64_t)lane * 2) : *(const uint8_t*)(vn + lane);
+    if constexpr (QUANT) {
+        r.ks = a.k_scale[(int64_t)b * a.H_kv + g + zero];
+        r.vs = a.v_scale[(int64_t)b * a.H_kv + g + zero];
     }
-    if (quant || EB == 2) r.vv = VD == 2 ? *(const uint32_t*)(vn + (int64_t)lane * 4) : *(const uint16_t*)(vn + (int64_t)lane * 2);
-    else r.vv = VD == 2 ? *(const uint16_t*)(vn + (int64_t)lane * 2) : *(const uint8_t*)(vn + lane);
-    r.ks = quant ? a.k_scale[(int64_t)b * a.H_kv + g] : 0.f;
-    r.vs = quant ? a.v_scale[(int64_t)b * a.H_kv + g] : 0.f;
-    return r;
 }
 
-template <int D, bool FP8>
+template <int D, bool FP8, bool QUANT>
 __device__ __forceinline__ void row_store(const AttnArgs& a, const NewRow& r, int lane) {
     constexpr int EB = FP8 ? 1 : 2;
     constexpr int X = 16 / EB;
     constexpr int VD = D / 64;
-    if ((unsigned)r.pg >= (unsigned)a.num_pages) return;
-    const bool quant = FP8 && a.quant;
+    if (r.slot < 0 || (unsigned)r.pg >= (unsigned)a.num_pages) return;
     char* kp = (char*)a.k_pages + ((int64_t)r.pg * a.H_kv + r.g) * ((int64_t)D * kPage * EB);
     char* vp = (char*)a.v_pages + ((int64_t)r.pg * a.H_kv + r.g) * ((int64_t)D * kPage * EB);
     if (lane < D / X) {
         u32x4 w = r.w;
-        if (quant) {   // 16 bf16 -> 16 e4m3fn codes with the K scale
+        if constexpr (QUANT) {   // 16 bf16 -> 16 e4m3fn codes with the K scale
             const uint32_t in[8] = {r.w.x, r.w.y, r.w.z, r.w.w, r.h.x, r.h.y, r.h.z, r.h.w};
             uint32_t ow[4];
 #pragma unroll
@@ -790,10 +790,10 @@ __device__ __forceinline__ void row_store(const AttnArgs& a, const NewRow& r, in
 #pragma unroll
     for (int i = 0; i < VD; ++i) {
         char* dst = vp + ((int64_t)(lane * VD + i) * kPage + r.slot) * EB;
-        if (quant) {
+        if constexpr (QUANT) {
             const uint32_t bits = (r.vv >> (16 * i)) & 0xffffu;
             *(uint8_t*)dst = (uint8_t)quantize_e4m3fn(__uint_as_float(bits << 16), r.vs);
-        } else if (EB == 2) {
+        } else if constexpr (EB == 2) {
             *(uint16_t*)dst = (uint16_t)(r.vv >> (16 * i));
         } else {
             *(uint8_t*)dst = (uint8_t)(r.vv >> (8 * i));
@@ -997,24 +997,52 @@ attn_mfma_kernel(AttnArgs a) {
     // another unit of the range, so the walk stays inside the batch.  The
     // stored length is the attention length less one below the table's end;
     // only a full-width attention length needs the stored one read back.
+    // The next row's reads are in flight while a row is stored: a round trip a
+    // row made shares of many short requests end late (512 requests with
+    // Zipf lengths to 32k over fp8 pools 449 -> 412 us at head_dim 64, to 16k
+    // at head_dim 128 564 -> 545; bf16 793 -> 770 and 1464 -> 1445).
     if constexpr (STEP) {
-        int b = sb, g = sg, L = sL, x0 = r0 - sp / PP;   // segment (b, g), its first unit x0
-        for (;;) {
-            const int last = x0 + ((L + kPage - 1) / kPage + PP - 1) / PP - 1;
-            if (last >= r1) break;                        // runs past the range: another wave's
-            const int Ls = L < maxL ? L - 1 : a.seq_lens[b];
-            if (Ls >= 0 && Ls < maxL) row_store<D, FP8>(a, row_load<D, FP8>(a, b, g, Ls, lane), lane);
-            x0 = last + 1;
-            if (x0 >= r1) break;
-            if (++g == a.H_kv) {
-                g = 0;
-                do {                                      // the next request with units
-                    ++b;
-                    L = attn_len<STEP>(a, a.seq_lens[b]);
-                } while (L == 0 && b + 1 < a.B);
-                if (L == 0) break;
+        auto write_rows = [&](auto quant) {
+            constexpr bool QUANT = decltype(quant)::value;
+            int zero;
+            asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
+            int b = sb, g = sg, L = sL, x0 = r0 - sp / PP;   // segment (b, g), its first unit x0
+            bool more = true;
+            auto next = [&](NewRow& r) {
+                if (!more) return false;
+                const int last = x0 + ((L + kPage - 1) / kPage + PP - 1) / PP - 1;
+                if (last >= r1) {                            // runs past the range: another wave's
+                    more = false;
+                    return false;
+                }
+                const int Ls = L < maxL ? L - 1 : a.seq_lens[b];
+                row_load<D, FP8, QUANT>(r, a, b, g, min(max(Ls, 0), maxL - 1), lane, zero);
+                if (Ls < 0 || Ls >= maxL) r.slot = -1;
+                x0 = last + 1;
+                if (x0 >= r1) {
+                    more = false;
+                } else if (++g == a.H_kv) {
+                    g = 0;
+                    do {                                     // the next request with units
+                        ++b;
+                        L = attn_len<STEP>(a, a.seq_lens[b]);
+                    } while (L == 0 && b + 1 < a.B);
+                    if (L == 0) more = false;
+                }
+                return true;
+            };
+            NewRow even, odd;
+            bool have = next(even);
+            while (have) {
+                const bool second = next(odd);
+                row_store<D, FP8, QUANT>(a, even, lane);
+                if (!second) break;
+                have = next(even);
+                row_store<D, FP8, QUANT>(a, odd, lane);
             }
-        }
+        };
+        if (FP8 && a.quant) write_rows(std::integral_constant<bool, FP8>{});
+        else write_rows(std::false_type{});
         // the rows are in memory before this wave reads any page
         __builtin_amdgcn_s_waitcnt(0);
     }

@@ -106,6 +106,27 @@ def test_step_matches_two_calls(case):
         assert b["sl"].cpu().tolist() == [L + 1 for L in lens]
 
 
+@pytest.mark.parametrize("kind", ["bf16", "fp8", "fp8q"])
+@pytest.mark.parametrize("D,H_q,H_kv", [(128, 8, 1), (64, 6, 3)])
+def test_step_shares_of_many_rows(kind, D, H_q, H_kv):
+    # a wave writes 1, 2, 3 and up to 24 rows ahead of its pages (the next
+    # row's reads under way while one is stored), over empty requests, requests
+    # whose table is full and shares that end inside a request
+    lens = [0, 1, 15, 16, 128, 31, 17, 40] * 3
+    base = _state(D + H_q, len(lens), H_q, H_kv, D, lens, kind)
+    scale = float(np.float32(1.0 / np.sqrt(D)))
+    base["sl"][5] = base["bt"].shape[1] * 16          # no room: the append refuses it
+    for waves in (1, 2, 3, 5, 24, 100, 0):
+        a, b = _clone(base), _clone(base)
+        _two_calls(a, scale, max_waves=waves)
+        torch.cuda.synchronize()
+        flags = bl.device_errors()
+        _step(b, scale, max_waves=waves)
+        torch.cuda.synchronize()
+        assert bl.device_errors() == flags
+        _same(a, b, f"{kind} D={D} waves={waves}")
+
+
 def test_step_many_short_requests():
     # 1500 requests (the planner's multi-batch path), lengths 0..40
     rng = np.random.default_rng(15)
