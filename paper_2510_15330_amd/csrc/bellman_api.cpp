@@ -42,7 +42,7 @@ constexpr int kXcdSkew2 = 6;          // the same with two workgroups per CU (fp
 constexpr int kMaxAttnBatch = 8192;  // lengths every attention wave reads to find its share
 constexpr double kShortSharePages = 512;   // below this many table pages a wave: short shares (see their use)
 constexpr double kShortSharePages64 = 64;  // the same for depth 1 at head_dim 64
-constexpr double kWideTablePages = 4096;   // fp8: from this many on, two workgroups a CU (see their use)
+constexpr double kWideTablePages = 3584;   // fp8: from this many on, two workgroups a CU (see their use)
 
 // The growable per-device workspace.  Growing it allocates a larger block
 // and keeps the old one alive until bellman_shutdown, so kernels already
@@ -378,10 +378,11 @@ int decode_attention(const bellman_tensor_t* q, const bellman_tensor_t* k_pages,
     // of 1-4k 71.8 / 66.3, 400 of 3-5k 514 / 504, 256 of 6-13.5k 767 / 757.
     // The widest tables mostly mean lengths that differ much, where shares of
     // many short requests take longer than shares of long ones and the second
-    // workgroup evens that out at up to 4 heads (1024 with Zipf lengths to 16k,
+    // workgroup evens that out at up to 8 heads (1024 with Zipf lengths to 16k,
     // 1 head 770 / 788, 2 heads 785 / 796, 4 heads 811 / 815, 8 heads 845 / 848,
-    // 16 heads 912 / 892); a table of that width over even lengths pays for it
-    // (600 of 3-5k 759 / 750).
+    // 16 heads 912 / 892; in the one-call decode step, whose shares write their
+    // requests' new rows, 965 / 1013 at 8 heads, 512 to 16k 490 / 537 at one); a
+    // table of that width over even lengths pays for it (600 of 3-5k 759 / 750).
     // At head_dim 64 a step has half the bytes to hide as much arithmetic
     // behind, and two win from short shares on, later the more heads there are
     // (512 with Zipf lengths to 32k 321 / 375 us at 4 heads, 352 / 378 at 16;
@@ -390,7 +391,7 @@ int decode_attention(const bellman_tensor_t* q, const bellman_tensor_t* k_pages,
     // 31.4 at 4 heads and 34.6 / 32.4 at 8).
     const bool two = chosen && ps.fp8 &&
                      (ps.D == 64 ? table_pages_per_wave >= std::max(96.0, 14.0 * (double)G)
-                                 : G <= 4 && table_pages_per_wave >= kWideTablePages);
+                                 : G <= 8 && table_pages_per_wave >= kWideTablePages);
     const int wgs = chosen && !two ? 1 : bpc;
     const int64_t cu_waves = (int64_t)g_cu_count[dev] * (kAttnBlock / kWaveSize);
     int64_t waves = cu_waves * wgs, sized = cu_waves * (depth == asked_depth ? bpc : 1);

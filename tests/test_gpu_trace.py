@@ -50,18 +50,18 @@ def test_traced_kernel_same_bits_and_records(name, pps, waves):
     assert bl.device_errors() == 0
 
 
-@pytest.mark.parametrize("H_q", [8, 16, 32])          # 2, 4 and 8 query heads a KV head
+@pytest.mark.parametrize("H_q", [8, 32, 36])          # 2, 8 and 9 query heads a KV head
 def test_fp8_workgroups_by_table_width(H_q):
-    # fp8 at head_dim 128: one workgroup a CU, two over a table of 4096 pages a
-    # wave or more at up to 4 heads; the options' own steps take two
+    # fp8 at head_dim 128: one workgroup a CU, two over a table of 3584 pages a
+    # wave or more at up to 8 heads; the options' own steps take two
     cus, B, H_kv = torch.cuda.get_device_properties(0).multi_processor_count, 4, 4
     g = torch.Generator(device="cuda").manual_seed(1)
     pages = torch.randint(0, 120, (2, 64, H_kv, 128 * 16), generator=g, dtype=torch.uint8, device="cuda")
     q = torch.randn((B, H_q, 128), generator=g, device="cuda").to(torch.bfloat16)
     scale = torch.full((B, H_kv), 0.01, device="cuda")
     lens = torch.full((B,), 200, dtype=torch.int32, device="cuda")
-    edge = 4096 * 4 * cus // (B * H_kv)
-    for width, kw, want in ((edge - 1, {}, 1), (edge, {}, 2 if H_q <= 16 else 1),
+    edge = 3584 * 4 * cus // (B * H_kv)
+    for width, kw, want in ((edge - 1, {}, 1), (edge, {}, 2 if H_q <= 32 else 1),
                             (13, dict(pages_per_step=4, pipeline_depth=1), 2)):
         bt = torch.full((B, width), -1, dtype=torch.int32, device="cuda")
         bt[:, :13] = torch.arange(B * 13, device="cuda").view(B, 13)
