@@ -313,7 +313,8 @@ int bellman_kv_write(const bellman_tensor_t *k_new, const bellman_tensor_t *v_ne
  * head over all of their keys, or over a share of them where the rows would
  * leave the device idle (merged in fp32 by a second pass).  QK^T runs on the
  * bf16 matrix cores and PV on the fp16 ones, in one pass with P rounded to
- * fp16 (11 significant bits; P rounded to bf16 once would spend the bf16
+ * fp16 (11 significant bits above 2^-14 of the row's largest weight, an
+ * absolute 2^-25 of it below; P rounded to bf16 once would spend the bf16
  * error budget).  Over bf16 pools the values the call reads are first copied
  * into the workspace as fp16, each 64-token step of a (request, KV head) at
  * the power of two 2^e that brings its largest magnitude M into

@@ -71,6 +71,7 @@ struct AttnArgs {
     int4* cuts;          // [waves]: (request, KV head, last wave, 0) of the (request, head) in
                          // which wave w's range ends if it began inside the range and runs past
                          // it, else request -1; written by the attention kernel for the merge
+                         // (the last word makes the record one 16-byte access)
     float2* part_ml;     // [2 * waves * G]: (running max in log2 units, sum) of each wave's two
                          // partial pieces (the request cut at its range's start, and at its end)
     float* part_o;       // [2 * waves * G * D]

@@ -242,14 +242,17 @@ __global__ void lens_kernel(WriteArgs a) {
 //
 // Up to 64 requests every wave plans for itself from the lengths, a request
 // a lane (a planning launch took 5-6 us, and what a workgroup read back from
-// it as many round trips); beyond, prefill_plan_kernel does (no key split).
+// it as many round trips); beyond, prefill_plan_kernel does (no key split: 64
+// requests of 30 new tokens after 500 take 56 us, 65 67, as against 100 and
+// 102 with rows of one query head each; 100 after 3,000 301 and 312 us).
 //
 // Measured, whole prompt steps, against rows of one query head each, no key
 // split and the planning launch: one 2048-token chunk after 4,900 tokens on
 // 4/2 heads (64 tiles: 512 units of 14 steps) 171 -> 56 us, the attention
 // alone 141 -> 41 us and 8 us of merge (256 units: 50 + 6 us); eight chats'
 // 16-256 new tokens after 2-8k (336 tiles instead of 416, 488 units) 205 ->
-// 163 us; four prompts of 6-12k (7584 tiles, never cut) 2017 -> 2006 us.
+// 163 us; four prompts of 6-12k (7584 tiles, never cut) 2017 and 2006 us,
+// within the spread of runs.
 struct ReqPlan {
     int q0, n, L, tiles, steps;   // steps: 64-key steps of its keys; 0 with no tiles
     bool bad;
@@ -399,7 +402,7 @@ __global__ void __launch_bounds__(kPlanThreads) prefill_plan_kernel(PrefillArgs 
 // four pages [D][16 slots] are contiguous, a request's steps consecutive,
 // slots past its length zero.  A scale a step needs one pass over the values
 // (a scale a (request, head) took three: the maximum of every tile, of every
-// (request, head), then the copy; 33 against 18 us on 36k tokens of 8 heads);
+// (request, head), then the copy; 46 against 32 us on 36k tokens of 8 heads);
 // the attention holds its output at the finest step's scale and works what a
 // coarser step's is below that into its weights.
 constexpr int kAnyExp = 1 << 20;   // the step's values are all zero: any scale holds
