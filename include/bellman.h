@@ -341,7 +341,8 @@ int bellman_prefill_attention(const bellman_tensor_t *q, const bellman_tensor_t 
 typedef struct bellman_prefill_opts {
     void *event_begin;    /* optional hipEvent_t recorded right before the attention
                              kernel (after the planning and value-copy kernels) */
-    void *event_end;      /* optional hipEvent_t recorded right after it */
+    void *event_end;      /* optional hipEvent_t recorded right after it (and after
+                             the merge, where keys are shared out) */
 } bellman_prefill_opts_t;
 
 /* bellman_prefill_attention with options (NULL = defaults). */
